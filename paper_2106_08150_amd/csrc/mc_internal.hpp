@@ -203,7 +203,7 @@ constexpr uint32_t kQsStride = 16;                     // u64 words between copi
 constexpr uint32_t kQsWords = kQsCopies * kQsStride;
 
 constexpr uint32_t kListSmall = 512;     // candidate locations per record, fast path
-constexpr uint32_t kListLarge = 16384;   // large-list pass (one wave per workgroup)
+constexpr uint32_t kListLarge = 16384;   // large-list pass (one workgroup per record)
 static_assert(kListLarge < 0x10000, "top-m keys pack a distinct-location index in 16 bits");
 constexpr uint32_t kMaxTopM = 8;
 

@@ -303,59 +303,24 @@ __device__ __forceinline__ void sort_regs(uint32_t* list, uint32_t n) {
     wave_lds_sync();
 }
 
-// Bitonic sort of list[0..P) in LDS by one wave (P a power of two, entries
-// n..P-1 padded with the largest key).
-__device__ void sort_lds(uint32_t* list, uint32_t n, uint32_t P) {
-    const uint32_t lane = (uint32_t)lane_id();
-    for (uint32_t e = n + lane; e < P; e += kWave) list[e] = 0xFFFFFFFFu;
-    wave_lds_sync();
-    for (uint32_t size = 2; size <= P; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            for (uint32_t idx = lane; idx < P / 2; idx += kWave) {
-                uint32_t i = (idx / stride) * 2 * stride + (idx % stride);
-                uint32_t j = i + stride;
-                bool asc = (i & size) == 0;
-                uint32_t x = list[i], y = list[j];
-                if ((x > y) == asc) {
-                    list[i] = y;
-                    list[j] = x;
-                }
-            }
-            wave_lds_sync();
-        }
-    }
-}
-
-// Lists of more than 128 locations.
-template <uint32_t LCAP>
-__device__ __forceinline__ void sort_list_long_body(uint32_t* list, uint32_t n) {
-    uint32_t P = 256;
-    while (P < n) P <<= 1;
-    switch (P) {
-        case 256: sort_regs<4>(list, n); break;
-        case 512: sort_regs<8>(list, n); break;
-        case 1024: if (LCAP >= 1024) sort_regs<16>(list, n); break;
-        default: sort_lds(list, n, P); break;
-    }
-}
-
-// The fast paths' copy is out of line (the hot loop stays small in the
-// instruction cache), with an LDS pointer so that the out-of-line code keeps
-// LDS instructions. The large-list pass, which every classification launches,
-// inlines it: there the out-of-line call needed a stack frame in scratch
-// memory.
+// Lists of more than 128 locations, out of line: the hot loop stays small in
+// the instruction cache. The pointer is an LDS pointer so that the out-of-line
+// code keeps LDS instructions.
 template <uint32_t LCAP>
 __device__ __attribute__((noinline)) void sort_list_long(MC_LDS uint32_t* lds_list, uint32_t n) {
-    sort_list_long_body<LCAP>((uint32_t*)lds_list, n);
+    uint32_t* const list = (uint32_t*)lds_list;
+    if (n <= 256) sort_regs<4>(list, n);
+    else if (n <= 512) sort_regs<8>(list, n);
+    else if constexpr (LCAP >= 1024) sort_regs<16>(list, n);
 }
 
-// Ascending sort of list[0..n) in LDS.
+// Ascending sort of list[0..n) in LDS (n <= LCAP <= 1024).
 template <uint32_t LCAP>
 __device__ __forceinline__ void sort_list(uint32_t* list, uint32_t n) {
+    static_assert(LCAP <= 1024, "longer lists take the large-list pass");
     if (n <= 64) sort_regs<1>(list, n);
     else if (n <= 128) sort_regs<2>(list, n);
-    else if constexpr (LCAP <= 1024) sort_list_long<LCAP>((MC_LDS uint32_t*)list, n);
-    else sort_list_long_body<LCAP>(list, n);
+    else sort_list_long<LCAP>((MC_LDS uint32_t*)list, n);
 }
 
 // Label and top-m list of a record (lane x writes the x-th top hit).
@@ -596,7 +561,7 @@ __device__ __forceinline__ void label_short_list(const QueryArgs& a, uint32_t re
 }
 
 template <uint32_t LCAP, int KPL, bool C>
-__device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>& L, bool big,
+__device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>& L,
                                 const Threshold& th, WaveStats& ws) {
     const int lane = lane_id();
     // the record's offsets by scalar loads (rec is wave-uniform; the array
@@ -631,7 +596,11 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
         nws[sg] = mate_windows32(a, rs.len[sg]);
     const uint32_t nwt = nws[0] + nws[1];
     uint32_t nlist = 0, nf = 0;
-    bool fits = true;
+    // a record with more sketch elements than the list holds most likely
+    // outgrows it (an element of a read from a stored genome has a location
+    // or more): it goes straight to the large-list pass, whose eight waves
+    // share its windows
+    bool fits = nwt * a.s <= LCAP;
     for (uint32_t p = 0; p < nwt && fits; p += 2) {
         WinRef wr[2];
         for (int h = 0; h < 2; ++h) wr[h] = window_ref(a, p + h, nwt, nws[0], rs.r0, rs.len);
@@ -666,13 +635,8 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
         }
     }
     if (!fits) {
-        // the fast path queues the record for the large-list pass, that pass
-        // for the HBM-list pass (ids from n_records on)
-        if (lane == 0) {
-            uint32_t* const counters = MC_COLD(counters);
-            const uint32_t qi = atomicAdd(&counters[big ? kQHuge : kQOverflow], 1u);
-            MC_COLD(queue)[(big ? MC_COLD(n_records) : 0u) + qi] = rec;
-        }
+        // queued for the large-list pass
+        if (lane == 0) MC_COLD(queue)[atomicAdd(&MC_COLD(counters)[kQOverflow], 1u)] = rec;
         ws.passed_on += 1;
         return;
     }
@@ -778,43 +742,39 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
 // occupancy pays for a few spilled scalar registers. A 512-entry list takes
 // about 5.7 KB of LDS a wave, which holds a CU to 28 waves: seven a SIMD (at
 // most 72 VGPRs). A 256-entry list takes about 3.7 KB, so eight waves a SIMD
-// fit (64 VGPRs). A 1,024-entry list (9.7 KB) allows four waves a SIMD and
-// the large-list pass (about 130 KB) one workgroup a CU: their register
-// budgets follow, so that no variant spills vector registers to scratch
-// memory (a kernel with scratch makes the runtime set up scratch for the
-// hardware queue it runs on, milliseconds on a queue's first such launch).
+// fit (64 VGPRs). A 1,024-entry list (9.7 KB) allows four waves a SIMD: its
+// register budget follows, so that no variant spills vector registers to
+// scratch memory (a kernel with scratch makes the runtime set up scratch for
+// the hardware queue it runs on, milliseconds on a queue's first such launch).
 // The condensed layout's lookups also fit eight waves at a 256-entry list
 // (63 VGPRs, more scalar spills than at seven, and 4% faster).
 template <uint32_t LCAP, bool C>
 constexpr int classify_waves_per_simd() {
-    return LCAP <= 256 ? 8 : LCAP <= 512 ? 7 : LCAP <= 1024 ? 4 : 1;
+    return LCAP <= 256 ? 8 : LCAP <= 512 ? 7 : 4;
 }
 
 template <uint32_t LCAP, int WPB, int KPL, bool C>
 __global__ __launch_bounds__(WPB * 64)
 __attribute__((amdgpu_waves_per_eu(classify_waves_per_simd<LCAP, C>())))
-void k_classify(QueryArgs a, int big, int cls) {
+void k_classify(QueryArgs a, int cls) {
     __shared__ QueryLds<LCAP> L[WPB];
     const int wave = (int)uniform(threadIdx.x >> 6);
     for (uint32_t i = (uint32_t)lane_id(); i < kRing + kRingMirror; i += kWave)
         L[wave].ring[i] = make_uint2(0u, 0u);   // any item must name a bucket of the table
     wave_lds_sync();
-    // the records of this launch: all of them, those queued for the large-list
-    // pass (big), or those of size class cls >= 0 (routed); the id arrays are
-    // read where they are used (no registers held across the record loop)
-    const uint32_t n_iter = big ? uniform(a.counters[kQOverflow])
-                                : cls >= 0 ? uniform(a.route_meta[cls]) : a.n_records;
+    // the records of this launch: all of them, or those of size class cls >= 0
+    // (routed); the id arrays are read where they are used (no registers held
+    // across the record loop)
+    const uint32_t n_iter = cls >= 0 ? uniform(a.route_meta[cls]) : a.n_records;
     WaveStats ws;
     const Threshold th(a.S, a.s);
     for (uint32_t it = blockIdx.x * WPB + wave; it < n_iter; it += gridDim.x * WPB) {
         uint32_t rec = it;
-        if (big) {
-            rec = uniform(MC_COLD(queue)[it]);
-        } else if (cls >= 0) {
+        if (cls >= 0) {
             const uint32_t* const meta = MC_COLD(route_meta);
             rec = uniform(MC_COLD(route_queue)[meta[kMaxRoutes + cls] + it]);
         }
-        classify_record<LCAP, KPL, C>(a, rec, L[wave], big != 0, th, ws);
+        classify_record<LCAP, KPL, C>(a, rec, L[wave], th, ws);
     }
     // work of records that go on to the large-list pass counts in both passes
     if (lane_id() == 0 && a.qstats) {
@@ -822,8 +782,496 @@ void k_classify(QueryArgs a, int big, int cls) {
         if (ws.features) atomicAdd(&q[kQsFeatures], (unsigned long long)ws.features);
         if (ws.locations) atomicAdd(&q[kQsLocations], (unsigned long long)ws.locations);
         if (ws.probes) atomicAdd(&q[kQsProbes], (unsigned long long)ws.probes);
-        if (ws.passed_on)
-            atomicAdd(&q[big ? kQsHuge : kQsLarge], (unsigned long long)ws.passed_on);
+        if (ws.passed_on) atomicAdd(&q[kQsLarge], (unsigned long long)ws.passed_on);
+    }
+}
+
+// ---------------------------------------------------- large-list pass -----
+// Records whose candidate list outgrew the fast path, up to kListLarge
+// locations: one workgroup of eight waves a record. The waves share the
+// record's windows (sketches into one feature buffer), its lookups (one list
+// in LDS) and its sort; 79 KB of LDS, so two workgroups a CU overlap each
+// other's phases. Bound by the latency of those phases at 16 waves a CU.
+//
+// One wave a record with a bitonic sort in LDS and a scan over each range (the
+// form this replaces) left most of the chip idle and took O(range) steps per
+// location: 20,000 reads of 0.8 to 10 kbp on 1 Gbp (11,530 records of about
+// 1,450 locations) 296 -> 0.97 ms, 4,000 mixed records on 300 identical genomes
+// (3,792 records of about 5,800) 336 -> 0.75 ms. Of that, sketches and lookups
+// take 0.70 and 0.41 ms, sorting and ranking 0.27 and 0.34 ms.
+constexpr int kLargeWaves = 8;
+constexpr int kLargeThreads = kLargeWaves * kWave;
+constexpr uint32_t kLargeFeats = 1024;   // sketch elements buffered before lookups
+
+struct LargeWave {
+    Word stage[2 * kStageWords];         // lookups of the condensed layout: runs
+    uint32_t scratch[kWave];
+    uint32_t sk[2 * 64];                 // sketches of a window pair
+};
+struct LargeLds {
+    uint32_t list[kListLarge];
+    uint32_t feats[kLargeFeats];
+    LargeWave wv[kLargeWaves];
+    uint32_t red[kLargeWaves];
+    uint32_t nfeat, nlist;
+    uint32_t sel_t[kMaxTopM], sel_s[kMaxTopM], sel_b[kMaxTopM];
+};
+static_assert(sizeof(LargeLds) <= 80 * 1024, "two workgroups a CU");
+
+// Place of list entry i: the low five index bits are swapped around by the
+// next five, so that neither the lanes' runs of consecutive entries (the
+// register sort) nor entries a power of two apart fall into one LDS bank.
+__device__ __forceinline__ uint32_t at(uint32_t i) { return i ^ ((i >> 5) & 31u); }
+
+// All 8 lanes of the groups whose last lane is set in `last`.
+__device__ __forceinline__ uint64_t groups_of(uint64_t last) {
+    const uint64_t first = last >> 7;
+    return (first << 8) - first;
+}
+
+// Append the locations of features F[0..nf) of the workgroup's buffer to the
+// list; called by all waves (no barrier inside). An 8-lane group takes NB
+// features and reads one bucket line of each at a time (kDeep: one feature,
+// NB consecutive buckets of its chain at a time, for few features with long
+// chains). L.nlist counts every location found, also past kListLarge (those
+// are not stored).
+template <bool kDeep>
+__device__ __forceinline__ void large_lookup(const QueryArgs& a, LargeLds& L, uint32_t nf,
+                                             uint32_t wave, uint32_t& probes) {
+    constexpr int NB = 4;
+    constexpr uint32_t kPerWave = kDeep ? 8u : 8u * NB;
+    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+    const uint32_t lane = (uint32_t)lane_id(), g = lane >> 3;
+    const u64x2* slot2 = reinterpret_cast<const u64x2*>(a.table) + (lane & 7u);
+    const uint32_t nb = (uint32_t)a.nb;
+    for (uint32_t i0 = wave * kPerWave; i0 < nf; i0 += kLargeWaves * kPerWave) {
+        uint32_t f[NB], b[NB];
+        uint64_t alive[NB];     // groups whose chain goes on (deep: of the one feature)
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const uint32_t i = i0 + (kDeep ? 0u : 8u * q) + g;
+            f[q] = L.feats[min(i, nf - 1u)];
+            alive[q] = ballot(i < nf);
+            b[q] = (uint32_t)home_bucket(f[q], a.nb);
+            if (kDeep) {
+                b[q] += (uint32_t)q;
+                if (b[q] >= nb) b[q] -= nb;
+            }
+        }
+        for (;;) {
+            u64x2 sl[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+                if (lane_in(alive[q])) sl[q] = slot2[(uint64_t)b[q] * (kSlots / 2)];
+            uint64_t hit0[NB], hit1[NB], any = 0;
+            uint32_t c = 0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                if (kDeep && q) alive[q] = alive[q - 1];
+                const unsigned long long s0 = sl[q].x, s1 = sl[q].y;
+                hit0[q] = alive[q] & ballot((uint32_t)(s0 >> 32) == f[q]) &
+                          ballot((uint32_t)s0 < kTombLoc);
+                hit1[q] = alive[q] & ballot((uint32_t)(s1 >> 32) == f[q]) &
+                          ballot((uint32_t)s1 < kTombLoc);
+                c += popc64(hit0[q]) + popc64(hit1[q]);
+                probes += popc64(alive[q] & kLastSlots);
+                // a chain ends at its first bucket that is not full
+                alive[q] = groups_of(alive[q] & kLastSlots & ballot((uint32_t)s1 != 0xFFFFFFFFu));
+                any |= alive[q];
+            }
+            if (kDeep) any = alive[NB - 1];
+            if (c) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&L.nlist, c);
+                base = uniform(base);
+                if (base + c > kListLarge) return;
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    if (lane_in(hit0[q])) L.list[at(rank_below(hit0[q], base))] = (uint32_t)sl[q].x;
+                    base += popc64(hit0[q]);
+                    if (lane_in(hit1[q])) L.list[at(rank_below(hit1[q], base))] = (uint32_t)sl[q].y;
+                    base += popc64(hit1[q]);
+                }
+            }
+            if (!any) break;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                if (kDeep) alive[q] = any;
+                b[q] += kDeep ? (uint32_t)NB : 1u;
+                if (b[q] >= nb) b[q] -= nb;
+            }
+        }
+    }
+}
+
+// The same from the condensed layout: a feature's one entry is inline or a
+// run of the value array; the runs of a step are copied by the whole wave with
+// one flat index (see lookup_cond).
+__device__ __forceinline__ void large_lookup_cond(const QueryArgs& a, LargeLds& L, uint32_t nf,
+                                                  uint32_t wave, uint32_t& probes) {
+    constexpr int NB = 4;
+    const uint32_t lane = (uint32_t)lane_id(), g = lane >> 3;
+    const uint4* ent = reinterpret_cast<const uint4*>(a.table) + (lane & 7u);
+    const uint32_t nb = (uint32_t)a.nb;
+    uint32_t* const runs = reinterpret_cast<uint32_t*>(L.wv[wave].stage);   // 96 words
+    for (uint32_t i0 = wave * 8u * NB; i0 < nf; i0 += kLargeWaves * 8u * NB) {
+        uint32_t f[NB], b[NB];
+        uint64_t alive[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const uint32_t i = i0 + 8u * q + g;
+            f[q] = L.feats[min(i, nf - 1u)];
+            alive[q] = ballot(i < nf);
+            b[q] = (uint32_t)home_bucket(f[q], a.nb);
+        }
+        for (;;) {
+            uint4 e[NB];
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+                if (lane_in(alive[q])) e[q] = ent[(uint64_t)b[q] * kCondEntries];
+            uint64_t hitA[NB], hitB[NB], any = 0;
+            uint32_t nrun = 0, c = 0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const uint64_t used = alive[q] & ballot(e[q].y != 0u);
+                const uint64_t mine = used & ballot(e[q].x == f[q]);
+                const uint64_t small = ballot(e[q].y <= kCondInline);
+                const uint64_t hitR = mine & ~small;
+                hitA[q] = mine & small;
+                hitB[q] = hitA[q] & ballot(e[q].y == 2u);
+                c += popc64(hitA[q]) + popc64(hitB[q]);
+                if (lane_in(hitR)) {
+                    const uint32_t r = nrun + rank_below(hitR);
+                    runs[3 * r + 0] = e[q].y;
+                    runs[3 * r + 1] = e[q].z;
+                    runs[3 * r + 2] = e[q].w;
+                }
+                nrun += popc64(hitR);
+                probes += popc64(alive[q] & kLastSlots);
+                // groups that did not find their feature in a full line go on
+                uint64_t gf = mine;
+                gf |= gf >> 1;
+                gf |= gf >> 2;
+                gf |= gf >> 4;
+                alive[q] = groups_of(used & kLastSlots & ~((gf & 0x0101010101010101ull) << 7));
+                any |= alive[q];
+            }
+            uint32_t incl = 0, cnt = 0, total = 0;
+            if (nrun) {   // lane r holds run r
+                wave_lds_sync();
+                cnt = lane < nrun ? runs[3 * lane + 0] : 0u;
+                incl = cnt;
+#pragma unroll
+                for (int d = 1; d < 32; d <<= 1) {
+                    const uint32_t y = shfl_idx(incl, lane >= (uint32_t)d ? (int)lane - d : (int)lane);
+                    if (lane >= (uint32_t)d) incl += y;
+                }
+                total = uniform(shfl_idx(incl, (int)nrun - 1));
+                wave_lds_sync();
+                // first position of run r (past the runs: above every position)
+                if (lane < 32u) runs[3 * lane] = lane < nrun ? incl - cnt : 0xFFFFFFFFu;
+                wave_lds_sync();
+            }
+            if (c + total) {
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&L.nlist, c + total);
+                base = uniform(base);
+                if (base + c + total > kListLarge) return;
+#pragma unroll
+                for (int q = 0; q < NB; ++q) {
+                    if (lane_in(hitA[q])) L.list[at(rank_below(hitA[q], base))] = e[q].z;
+                    base += popc64(hitA[q]);
+                    if (lane_in(hitB[q])) L.list[at(rank_below(hitB[q], base))] = e[q].w;
+                    base += popc64(hitB[q]);
+                }
+                for (uint32_t i = lane; i < total; i += kWave) {
+                    uint32_t r = 0;   // the last run whose first position is <= i
+#pragma unroll
+                    for (uint32_t step = 16; step > 0; step >>= 1)
+                        if (runs[3 * (r + step)] <= i) r += step;
+                    const uint64_t off = ((uint64_t)runs[3 * r + 2] << 32) | runs[3 * r + 1];
+                    L.list[at(base + i)] = a.cval[off + (i - runs[3 * r])];
+                }
+                wave_lds_sync();
+            }
+            if (!any) break;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) b[q] = b[q] + 1u == nb ? 0u : b[q] + 1u;
+        }
+    }
+}
+
+// Compare-exchange steps of strides top/2, top/4, ..., 1 (all ascending) of a
+// bitonic merge; element lane * K + r of the wave in v[r]. top <= 64 * K.
+template <int K>
+__device__ __forceinline__ void merge_steps(uint32_t (&v)[K], int top) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int stride = 32 * K; stride >= K; stride >>= 1) {
+        if (stride >= top) continue;
+        const bool low = (lane & (stride / K)) == 0;
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            const uint32_t o = xor_lanes_c(v[r], stride / K);
+            const uint32_t lo = v[r] < o ? v[r] : o, hi = v[r] < o ? o : v[r];
+            v[r] = low ? lo : hi;
+        }
+    }
+#pragma unroll
+    for (int stride = K / 2; stride >= 1; stride >>= 1) {
+        if (stride >= top) continue;
+#pragma unroll
+        for (int r = 0; r < K; ++r) {
+            if (r & stride) continue;
+            const uint32_t x = v[r], y = v[r + stride];
+            v[r] = x < y ? x : y;
+            v[r + stride] = x < y ? y : x;
+        }
+    }
+}
+
+// Ascending sort of a wave's 64 * K keys (element lane * K + r in v[r]). Steps
+// of strides below K stay inside a lane (one minimum and one maximum a pair),
+// so most of the network needs no lane exchange. Descending blocks are sorted
+// ascending with their keys complemented.
+template <int K>
+__device__ __forceinline__ void sort_blocked(uint32_t (&v)[K]) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int size = 2; size < K; size <<= 1) {
+#pragma unroll
+        for (int stride = size / 2; stride >= 1; stride >>= 1)
+#pragma unroll
+            for (int r = 0; r < K; ++r) {
+                if (r & stride) continue;
+                const uint32_t x = v[r], y = v[r + stride];
+                const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
+                v[r] = (r & size) ? hi : lo;
+                v[r + stride] = (r & size) ? lo : hi;
+            }
+    }
+#pragma unroll
+    for (int size = K < 2 ? 2 : K; size <= 64 * K; size <<= 1) {
+        const uint32_t flip = size < 64 * K && (lane & (size / K)) != 0 ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int r = 0; r < K; ++r) v[r] ^= flip;
+        merge_steps<K>(v, size);
+#pragma unroll
+        for (int r = 0; r < K; ++r) v[r] ^= flip;
+    }
+}
+
+// The steps Q5-Q8 of a record whose n locations are in L.list, n <= 512 * K:
+// bitonic sort by the workgroup (each wave sorts 64 * K entries in registers;
+// the three merge levels across the eight waves start with one pass in which
+// a thread holds the eight entries of a column, one per wave's run), then for
+// each distinct location, at its first entry i of the sorted list, the score
+// of its range as (first entry past the range) - i by binary search, and the
+// top-m rounds on score << 16 | (0xFFFF - i), kept in registers.
+template <int K>
+__device__ __forceinline__ void large_rank(const QueryArgs& a, LargeLds& L, uint32_t rec,
+                                           uint32_t n, uint32_t sws) {
+    constexpr uint32_t kRun = 64 * K, P = kLargeThreads * K;
+    // (entry places are computed for this record, not held across the records)
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const uint32_t lane = tid & 63u, wave = uniform(tid >> 6);
+    // the first of the lane's entries, anew for every pass over them (the
+    // entries' places are not kept in registers from one pass to the next)
+    auto first_entry = [&]() -> uint32_t {
+        uint32_t e = wave * kRun + lane * K;
+        asm volatile("" : "+v"(e));
+        return e;
+    };
+    auto store_run = [&](const uint32_t (&v)[K], uint32_t desc) {
+        const uint32_t e0 = first_entry();
+#pragma unroll
+        for (int r = 0; r < K; ++r) L.list[at(e0 + r)] = v[r] ^ desc;
+    };
+    {
+        uint32_t v[K];
+        const uint32_t desc = (wave & 1u) ? 0xFFFFFFFFu : 0u, e0 = first_entry();
+#pragma unroll
+        for (int r = 0; r < K; ++r) v[r] = (e0 + r < n ? L.list[at(e0 + r)] : 0xFFFFFFFFu) ^ desc;
+        sort_blocked<K>(v);
+        store_run(v, desc);
+    }
+#pragma unroll
+    for (uint32_t m = 2; m <= (uint32_t)kLargeWaves; m <<= 1) {   // runs of m * kRun entries
+        __syncthreads();
+        for (uint32_t j = tid; j < kRun; j += kLargeThreads) {
+            uint32_t x[kLargeWaves];
+#pragma unroll
+            for (uint32_t c = 0; c < (uint32_t)kLargeWaves; ++c) x[c] = L.list[at(c * kRun + j)];
+#pragma unroll
+            for (uint32_t st = m / 2; st >= 1; st >>= 1)
+#pragma unroll
+                for (uint32_t c = 0; c < (uint32_t)kLargeWaves; ++c) {
+                    if (c & st) continue;
+                    const uint32_t p = x[c], q = x[c + st];
+                    const uint32_t lo = p < q ? p : q, hi = p < q ? q : p;
+                    x[c] = (c & m) ? hi : lo;
+                    x[c + st] = (c & m) ? lo : hi;
+                }
+#pragma unroll
+            for (uint32_t c = 0; c < (uint32_t)kLargeWaves; ++c) L.list[at(c * kRun + j)] = x[c];
+        }
+        __syncthreads();
+        uint32_t v[K];
+        const uint32_t desc = m < (uint32_t)kLargeWaves && (wave & m) ? 0xFFFFFFFFu : 0u;
+        const uint32_t e0 = first_entry();
+#pragma unroll
+        for (int r = 0; r < K; ++r) v[r] = L.list[at(e0 + r)] ^ desc;
+        merge_steps<K>(v, (int)kRun);
+        store_run(v, desc);
+    }
+    __syncthreads();
+
+    uint32_t key[K];
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        // (at most four searches in flight: more would not fit the registers)
+        if (r % 4 == 0) asm volatile("" ::: "memory");
+        const uint32_t i = (uint32_t)r * kLargeThreads + tid;
+        key[r] = 0u;
+        const uint32_t loc = L.list[at(i)];
+        if (i < n && (i == 0u || L.list[at(i - 1u)] != loc)) {
+            const uint32_t w = loc & kWindowMask;
+            const uint32_t lim = loc - w + min(w + sws, 1u << kWindowBits);
+            uint32_t end = 0;      // entries below lim (lim is at most the padding key)
+#pragma unroll
+            for (uint32_t step = P / 2; step > 0; step >>= 1)
+                if (L.list[at(end + step - 1u)] < lim) end += step;
+            if (L.list[at(end)] < lim) end += 1u;
+            key[r] = ((end - i) << 16) | (0xFFFFu - i);
+        }
+    }
+    uint32_t nsel = 0;
+    const uint32_t top_m = MC_COLD(top_m);
+    TopStop decided{MC_COLD(out_top) != nullptr, MC_COLD(min_hits), MC_COLD(hit_diff)};
+    for (uint32_t m = 0; m < top_m; ++m) {
+        uint32_t best = 0;
+#pragma unroll
+        for (int r = 0; r < K; ++r) best = key[r] > best ? key[r] : best;
+        best = wave_max_u32(best);
+        __syncthreads();
+        if (lane == 0) L.red[wave] = best;
+        __syncthreads();
+        best = L.red[lane & (kLargeWaves - 1)];
+        best = wave_max_u32(best);
+        if (best == 0u) break;
+        const uint32_t loc = uniform(L.list[at(0xFFFFu - (best & 0xFFFFu))]);
+        if (tid == 0) {
+            L.sel_t[m] = loc >> kWindowBits;
+            L.sel_s[m] = best >> 16;
+            L.sel_b[m] = loc & kWindowMask;
+        }
+        nsel = m + 1;
+        if (decided(m, best >> 16)) break;
+        uint32_t t = tid;               // the entries' places are not kept across the rounds
+        asm volatile("" : "+v"(t));
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+            if (L.list[at((uint32_t)r * kLargeThreads + t)] >> kWindowBits == loc >> kWindowBits)
+                key[r] = 0u;
+    }
+    if (wave == 0) {
+        wave_lds_sync();
+        write_result(a, rec, label_of(a, L, nsel), L, nsel);
+    }
+}
+
+template <int KPL, bool C>
+__device__ void classify_large_record(const QueryArgs& a, uint32_t rec, LargeLds& L,
+                                      const Threshold& th, WaveStats& ws) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = uniform(tid >> 6);
+    typedef const __attribute__((address_space(4))) uint64_t ConstU64;
+    ConstU64* const off = (ConstU64*)(uintptr_t)a.offsets;
+    uint64_t o0, o1, o2;
+    if (a.paired) {
+        o0 = off[2ull * rec]; o1 = off[2ull * rec + 1]; o2 = off[2ull * rec + 2];
+    } else {
+        o0 = off[rec]; o1 = off[rec + 1ull]; o2 = o1;
+    }
+    RecordSpan rs;
+    (void)record_span(a, o0, o1, o2, rs);   // queued records are well formed and span < 2^31 bytes
+    const uint32_t len = rs.len[0] + rs.len[1];
+    const uint32_t F = rs.len[0] > 0 && rs.len[1] > 0 && a.insert_size > len ? a.insert_size : len;
+    const uint32_t sws = fragment_sws32(a, F);
+    const uint32_t nw0 = mate_windows32(a, rs.len[0]), nwt = nw0 + mate_windows32(a, rs.len[1]);
+    const uint32_t per_round = (kLargeFeats / a.s) & ~1u;   // windows whose sketches fit the buffer
+    __syncthreads();                       // the previous record is done with the LDS
+    if (tid == 0) L.nlist = 0;
+    for (uint32_t p0 = 0; p0 < nwt; p0 += per_round) {
+        if (tid == 0) L.nfeat = 0;
+        __syncthreads();
+        const uint32_t p1 = min(nwt, p0 + per_round);
+        LargeWave& W = L.wv[wave];
+        for (uint32_t p = p0 + 2u * wave; p < p1; p += 2u * kLargeWaves) {
+            WinRef wr[2];
+            for (int h = 0; h < 2; ++h) wr[h] = window_ref(a, p + h, p1, nw0, rs.r0, rs.len);
+            wave_lds_sync();
+            bool dirtyA, dirtyB;
+            stage_pair(W.stage, rs.base, wr[0], wr[1], (int)lane, dirtyA, dirtyB);
+            wave_lds_sync();
+            uint32_t nA, nB;
+            sketch_pair<KPL>(W.stage, wr[0].x0, wr[0].nk, W.stage + kStageWords, wr[1].x0,
+                             wr[1].nk, a.k, a.s, th, W.sk, W.sk + 64, W.scratch, nA, nB, dirtyA,
+                             dirtyB);
+            wave_lds_sync();
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&L.nfeat, nA + nB);
+            base = uniform(base);
+            if (lane < nA) L.feats[base + lane] = W.sk[lane];
+            if (lane < nB) L.feats[base + nA + lane] = W.sk[64 + lane];
+        }
+        __syncthreads();
+        const uint32_t nf = uniform(L.nfeat);
+        if (nf) {
+            if (wave == 0) ws.features += nf;
+            if constexpr (C) large_lookup_cond(a, L, nf, wave, ws.probes);
+            else if (nf <= 8u * kLargeWaves) large_lookup<true>(a, L, nf, wave, ws.probes);
+            else large_lookup<false>(a, L, nf, wave, ws.probes);
+        }
+        __syncthreads();
+        if (uniform(L.nlist) > kListLarge) break;
+    }
+    __syncthreads();
+    const uint32_t n = uniform(L.nlist);
+    if (n > kListLarge) {                  // queued for the HBM-list pass (ids from n_records on)
+        if (tid == 0) {
+            const uint32_t qi = atomicAdd(&a.counters[kQHuge], 1u);
+            a.queue[a.n_records + qi] = rec;
+            ws.passed_on += 1;
+        }
+        return;
+    }
+    if (wave == 0) ws.locations += n;
+    if (n <= 2 * kLargeThreads) large_rank<2>(a, L, rec, n, sws);
+    else if (n <= 4 * kLargeThreads) large_rank<4>(a, L, rec, n, sws);
+    else if (n <= 8 * kLargeThreads) large_rank<8>(a, L, rec, n, sws);
+    else if (n <= 16 * kLargeThreads) large_rank<16>(a, L, rec, n, sws);
+    else large_rank<32>(a, L, rec, n, sws);
+}
+
+template <int KPL, bool C>
+__global__ __launch_bounds__(kLargeThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_classify_large(QueryArgs a) {
+    __shared__ LargeLds L;
+    const uint32_t n_iter = uniform(a.counters[kQOverflow]);
+    if (blockIdx.x >= n_iter) return;
+    WaveStats ws;
+    const Threshold th(a.S, a.s);
+    for (uint32_t it = blockIdx.x; it < n_iter; it += gridDim.x)
+        classify_large_record<KPL, C>(a, uniform(a.queue[it]), L, th, ws);
+    // work of records that go on to the HBM-list pass counts in both passes
+    if (lane_id() == 0 && a.qstats) {
+        unsigned long long* q =
+            a.qstats + ((blockIdx.x * kLargeWaves + (threadIdx.x >> 6)) % kQsCopies) * kQsStride;
+        if (ws.features) atomicAdd(&q[kQsFeatures], (unsigned long long)ws.features);
+        if (ws.locations) atomicAdd(&q[kQsLocations], (unsigned long long)ws.locations);
+        if (ws.probes) atomicAdd(&q[kQsProbes], (unsigned long long)ws.probes);
+        if (ws.passed_on) atomicAdd(&q[kQsHuge], (unsigned long long)ws.passed_on);
     }
 }
 
@@ -1144,7 +1592,7 @@ hipError_t launch_fast_t(const QueryArgs& a, uint32_t max_blocks, int cls, hipSt
     if (blocks > max_blocks) blocks = max_blocks;
     if (blocks < 1) blocks = 1;
     hipLaunchKernelGGL((k_classify<LCAP, WPB, KPL, C>), dim3((unsigned)blocks), dim3(WPB * 64), 0,
-                       st, a, 0, cls);
+                       st, a, cls);
     return hipGetLastError();
 }
 
@@ -1247,26 +1695,21 @@ __global__ __launch_bounds__(256) void k_route_scatter(QueryArgs a, RouteConfig 
     }
 }
 
-// Workgroups of the large-list pass: one a CU at most (its list takes most of
-// a CU's LDS), one per 4,096 records of the launch, 8 to 512. A workgroup of
-// this pass can start only on a CU that every other kernel's groups have
-// left, so a pass launched next to other batches' kernels (a served mix)
-// drains the CUs it is given; the records it takes are rare (none at all in
-// the configured workloads, whose lists stay within the fast path's
-// capacity), so it is kept small.
+// Workgroups of the large-list pass when the number of queued records is not
+// known on the host: as many as fit the chip at once (two a CU), at most one a
+// record. Without queued records they end at once: 512 of them cost no more
+// than 8 did (10,000 short reads: 25.6 us a call with either).
 inline unsigned large_pass_groups(uint32_t n_records) {
-    return (unsigned)std::min<uint32_t>(512u, std::max<uint32_t>(8u, n_records / 4096u));
+    return (unsigned)std::min<uint32_t>(512u, n_records);
 }
 
 template <bool C>
 void launch_large_c(const QueryArgs& a, uint32_t groups, hipStream_t st) {
     const dim3 grid(groups ? std::min<uint32_t>(groups, 512u) : large_pass_groups(a.n_records));
-    if (a.S <= 64)
-        hipLaunchKernelGGL((k_classify<kListLarge, 1, 1, C>), grid, dim3(64), 0, st, a, 1, -1);
-    else if (a.S <= 128)
-        hipLaunchKernelGGL((k_classify<kListLarge, 1, 2, C>), grid, dim3(64), 0, st, a, 1, -1);
+    if (a.S <= 128)
+        hipLaunchKernelGGL((k_classify_large<2, C>), grid, dim3(kLargeThreads), 0, st, a);
     else
-        hipLaunchKernelGGL((k_classify<kListLarge, 1, 4, C>), grid, dim3(64), 0, st, a, 1, -1);
+        hipLaunchKernelGGL((k_classify_large<4, C>), grid, dim3(kLargeThreads), 0, st, a);
 }
 
 }  // namespace
