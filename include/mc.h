@@ -315,7 +315,7 @@ int mc_classify_graph_destroy(mc_graph* g);
  * release_table = 1: the bucket table is freed (the query-only form): adds and
  *   mc_db_reserve then fail with MC_ERR_STATE; mc_db_dump reads the condensed
  *   layout; mc_db_get_stats reports its counts (no buckets, no tombstones).
- * Device memory during the call: the layout itself plus 12 bytes per 256
+ * Device memory during the call: the layout itself plus 18 bytes per 256
  * buckets of the table. Errors: MC_ERR_STATE (table already released),
  * MC_ERR_CAPACITY (more than 8,192 entries homed in 256 consecutive buckets,
  * which a table at the library's load factors does not reach), MC_ERR_OOM. */
@@ -339,7 +339,9 @@ int mc_db_get_stats(mc_db* db, mc_db_stats* out);
  *   chunk_slots    most pair slots of one build chunk;
  *   fail_after     1 = the next add reports MC_ERR_TABLE_FULL after all its
  *                  inserts ran, so that tests reach the rollback (the flag
- *                  clears itself).
+ *                  clears itself);
+ *   defer_entries  mc_db_condense: first size of its list of features that do
+ *                  not fit their slice's index buckets.
  * MC_ERR_INVALID_ARG for slice_shift outside 4..13 (0 excepted). */
 typedef struct mc_insert_path {
     uint32_t global_insert;
@@ -350,7 +352,7 @@ typedef struct mc_insert_path {
     uint32_t direct;
     uint64_t chunk_slots;
     uint32_t fail_after;
-    uint32_t reserved;
+    uint32_t defer_entries;
 } mc_insert_path;
 int mc_db_set_insert_path(mc_db* db, const mc_insert_path* path);
 

@@ -77,7 +77,7 @@ class InsertPath(C.Structure):
                 ("slice_shift", C.c_uint32), ("fine_bits", C.c_uint32),
                 ("stage_entries", C.c_uint32), ("direct", C.c_uint32),
                 ("chunk_slots", C.c_uint64), ("fail_after", C.c_uint32),
-                ("reserved", C.c_uint32)]
+                ("defer_entries", C.c_uint32)]
 
 
 class LaunchConfig(C.Structure):

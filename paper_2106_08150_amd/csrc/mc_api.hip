@@ -54,6 +54,9 @@ constexpr uint64_t kKeepScratchBytes = 512ull << 20;   // build scratch kept aft
 constexpr uint64_t kMaxChunkSlots = 1ull << 32;
 constexpr uint64_t kPartBytes = 256ull << 20;           // target table bytes per partition
 constexpr uint64_t kMinBuckets = 64;
+// Tables have whole conversion slices (mc_db_condense): the slices of the table
+// and of the condensed index then hold the same features.
+constexpr uint64_t kBucketStep = 1ull << kCondSliceShift;
 constexpr uint64_t kCandCapMax = 1ull << 24;
 
 // Launch plan of the fast path: size classes and one shape per class (one
@@ -308,7 +311,7 @@ int ensure_capacity(mc_db* db, uint64_t extra, hipStream_t st, bool defer_fill =
     if (db->table && (double)need <= db->load * slots_per_bucket * (double)db->nb) return MC_OK;
     uint64_t nb = (uint64_t)std::ceil((double)need / (db->load * slots_per_bucket));
     if (db->table) nb = std::max<uint64_t>(nb, db->nb + db->nb / 2);   // grow by >= 1.5x
-    nb = std::max<uint64_t>(nb, kMinBuckets);
+    nb = (std::max<uint64_t>(nb, kMinBuckets) + kBucketStep - 1) / kBucketStep * kBucketStep;
     // bucket indices are 32-bit in the query kernels (2^32 buckets = 512 GiB)
     if (nb > 0xFFFFFFFFull)
         return fail(MC_ERR_OOM, "table of %llu buckets exceeds 2^32 - 1", (unsigned long long)nb);
@@ -1294,56 +1297,59 @@ int mc_db_condense(mc_db* db, int release_table) {
     CondArgs c{};
     c.table = db->table;
     c.nb = db->nb;
-    c.n_slices = (uint32_t)(((db->nb - 1) >> kCondSliceShift) + 1);
-    unsigned long long* tf = nullptr;
-    int rc = dev_alloc(&c.slice_feats, c.n_slices);
+    c.n_slices = (uint32_t)(db->nb >> kCondSliceShift);
+    int rc = dev_alloc(&c.slice_cnt, c.n_slices);
     if (!rc) rc = dev_alloc(&c.slice_vals, (uint64_t)c.n_slices + 1);
-    if (!rc) rc = dev_alloc(&c.err, 2);
-    if (!rc) rc = dev_alloc(&tf, 1);
+    if (!rc) rc = dev_alloc(&c.res, 1);
     auto release = [&]() {
-        (void)dev_free(c.slice_feats);
+        (void)dev_free(c.slice_cnt);
         (void)dev_free(c.slice_vals);
-        (void)dev_free(c.err);
-        (void)dev_free(tf);
-        (void)dev_free(c.fill);
+        (void)dev_free(c.res);
+        (void)dev_free(c.defer);
     };
     if (rc) { release(); return rc; }
-    uint32_t err[2] = {0, 0};
-    unsigned long long total_feats = 0, total_vals = 0;
-    hipError_t e = launch_fill_u32(c.err, 2, 0u, nullptr);
-    if (e == hipSuccess) e = launch_condense_count(c, nullptr);
-    if (e == hipSuccess) e = launch_condense_scan(c, tf, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(err, c.err, sizeof err, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&total_feats, tf, 8, hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&total_vals, c.slice_vals + c.n_slices, 8,
-                                       hipMemcpyDeviceToHost);
+    CondResult r{};
+    hipError_t e = launch_condense_count(c, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(&r, c.res, sizeof r, hipMemcpyDeviceToHost);
     if (e != hipSuccess) { release(); return fail(MC_ERR_HIP, "condense: %s", hipGetErrorString(e)); }
-    if (err[0]) {
+    if (r.most > kCondCap) {
         release();
         return fail(MC_ERR_CAPACITY, "a slice of %u buckets holds more than %u entries",
                     1u << kCondSliceShift, kCondCap);
     }
-    // index buckets for about four entries of eight each (load 0.5)
-    c.nbc = std::max<uint64_t>(kMinBuckets, (total_feats + 3) / 4);
+    // index buckets for about four entries of eight each (load 0.5), the same
+    // number for every slice
+    c.per_slice = (uint32_t)std::max<uint64_t>(
+        (std::max<uint64_t>(kMinBuckets, (r.feats + 3) / 4) + c.n_slices - 1) / c.n_slices, 1);
+    c.nbc = (uint64_t)c.n_slices * c.per_slice;
     if (c.nbc > 0xFFFFFFFFull) { release(); return fail(MC_ERR_OOM, "index too large"); }
+    // deferred features: hardly any (at load 0.5 about one slice in 50 has
+    // one); a list that proves too short is made anew and the pass repeated
+    c.defer_cap = c.n_slices / 8 + 64;
+    if (db->ipath.defer_entries) c.defer_cap = db->ipath.defer_entries;   // forced (tests)
     rc = dev_alloc(&c.idx, c.nbc * kCondEntries * 4);
-    if (!rc) rc = dev_alloc(&c.fill, c.nbc);
-    if (!rc) rc = dev_alloc(&c.val, std::max<uint64_t>(total_vals, 1));
-    if (rc) {
-        (void)dev_free(c.idx);
-        (void)dev_free(c.val);
-        release();
-        return rc;
+    if (!rc) rc = dev_alloc(&c.val, std::max<uint64_t>(r.vals, 1));
+    for (bool again = true; again && !rc && e == hipSuccess;) {
+        rc = dev_alloc(&c.defer, c.defer_cap);
+        if (rc) break;
+        e = launch_fill_u64(&c.res->deferred, 1, 0ull, nullptr);
+        if (e == hipSuccess) e = launch_condense_write(c, r.most, nullptr);
+        CondResult w{};
+        if (e == hipSuccess) e = hipMemcpy(&w, c.res, sizeof w, hipMemcpyDeviceToHost);
+        r.failed = w.failed;
+        again = w.deferred > c.defer_cap;
+        if (again) {
+            (void)dev_free(c.defer);
+            c.defer = nullptr;
+            c.defer_cap = w.deferred;
+            if (e == hipSuccess) e = launch_fill_u32(&c.res->failed, 1, 0u, nullptr);
+        }
     }
-    e = launch_fill_u64(reinterpret_cast<unsigned long long*>(c.idx), c.nbc * kCondEntries * 2, 0ull,
-                        nullptr);
-    if (e == hipSuccess) e = launch_fill_u32(c.fill, c.nbc, 0u, nullptr);
-    if (e == hipSuccess) e = launch_condense_write(c, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(err, c.err, sizeof err, hipMemcpyDeviceToHost);
-    if (e != hipSuccess || err[1]) {
+    if (rc || e != hipSuccess || r.failed) {
         (void)dev_free(c.idx);
         (void)dev_free(c.val);
         release();
+        if (rc) return rc;
         if (e != hipSuccess) return fail(MC_ERR_HIP, "condense: %s", hipGetErrorString(e));
         return fail(MC_ERR_TABLE_FULL, "condensed index without a free entry");
     }
@@ -1351,21 +1357,10 @@ int mc_db_condense(mc_db* db, int release_table) {
     db->cidx = c.idx;
     db->nbc = c.nbc;
     db->cval = c.val;
-    db->cval_n = total_vals;
-    db->c_features = total_feats;
+    db->cval_n = r.vals;
+    db->c_features = r.feats;
+    db->c_pairs = r.pairs;
     db->version += 1;
-    // pairs stored: features with one or two locations hold them inline
-    {
-        unsigned long long* cnt = nullptr;
-        if (dev_alloc(&cnt, 1) == MC_OK) {
-            unsigned long long n = 0;
-            if (launch_fill_u64(cnt, 1, 0ull, nullptr) == hipSuccess &&
-                launch_condense_pairs(db->cidx, db->nbc, cnt, nullptr) == hipSuccess &&
-                hipMemcpy(&n, cnt, 8, hipMemcpyDeviceToHost) == hipSuccess)
-                db->c_pairs = n;
-            (void)dev_free(cnt);
-        }
-    }
     if (release_table) {
         HIP_TRY(dev_free(db->table));
         HIP_TRY(dev_free(db->bcount));

@@ -7,11 +7,23 @@
 //
 // The conversion works on slices of 2^kCondSliceShift bucket-table buckets:
 // all entries homed in a slice lie in its buckets or in the few buckets its
-// chains run on into, so a workgroup gathers them, sorts them by (feature,
-// location) in LDS and sees each feature's locations together. A count pass
-// sizes the index and the value array; the write pass redoes the gather and
-// sort, writes the runs at the slice's prefix of values and claims one index
-// entry per feature with a per-bucket fill counter.
+// chains run on into. The index has a whole number of buckets per slice
+// (per_slice), and both home buckets are the high part of h2(feature) times
+// the number of buckets, so the features homed in slice z of the table are
+// those homed in index buckets [z, z + 1) * per_slice, and no other workgroup
+// writes them. A workgroup gathers a slice's entries into LDS grouped by home
+// bucket (a counting sort: about six entries a bucket), and every entry finds
+// its feature's count and its own rank by comparing itself with the entries of
+// its bucket. A count pass sizes the index and the value array; the write pass
+// places the slice's features by a max-plus scan over its index buckets (as the
+// slice insert of the build does) and writes every index line once.
+//
+// Bound by vector issue (about 75% of its peak) and the bytes: two passes over
+// the table, the index written once. The form this replaces sorted each slice's
+// 64-bit entries in LDS twice, claimed every index entry with a global atomic
+// and cleared the index first: a 1 Gbp table (2.3 GB, 141.6M pairs) took 9.8 ms
+// to count, 11.3 to write and 1.7 for the clearing, the scan and the pair count;
+// now 0.68 + 1.79 + 0.09 ms (5.9 GB moved by the write pass, 3.3 TB/s).
 #include "mc_device.hpp"
 #include "mc_internal.hpp"
 
@@ -19,21 +31,39 @@ namespace mc {
 
 namespace {
 
-constexpr int kCondThreads = 1024;
+constexpr int kCondThreads = 512;
 constexpr uint32_t kCondWaves = kCondThreads / kWave;
+constexpr uint32_t kCondBuckets = 1u << kCondSliceShift;
+constexpr uint32_t kCondSlots = kCondBuckets * kSlots;
+constexpr uint32_t kCondMaxPer = kCondSlots / 4;       // index buckets a slice at most
+// Bins of a slice: an entry is compared with the others of its bin, and a wave
+// takes as long as its largest bin, so buckets are split into finer bins by the
+// next bits of the home bucket's product (four a table bucket in the count
+// pass, up to four an index bucket in the write pass: conversion of a 1 Gbp
+// table 3.1 -> 2.5 ms).
+constexpr uint32_t kCondBinSplit = 2;                  // log2, most
+constexpr uint32_t kCondCountBins = kCondBuckets << kCondBinSplit;
+constexpr uint32_t kCondWriteBins = 2048;
+constexpr int kCondHeld = (int)(kCondSlots / kCondThreads);   // slots a thread holds
+// Entries of one slice in the write pass's usual form: a table at the default
+// load holds about 2,048 (at most 4,096 slots); slices beyond it take the
+// kCondCap form. 52 KB of LDS against 120 KB: three workgroups a CU, not one.
+constexpr uint32_t kCondMid = 2944;
+// A bucket with more entries is sorted by the workgroup: the comparisons of
+// every entry with all others of its bucket grow with the square.
+constexpr uint32_t kCondLong = 64;
+constexpr uint32_t kCondMaxLong = kCondCap / (kCondLong + 1) + 1;
 
-struct CondLds {
-    unsigned long long key[kCondCap];   // feature << 32 | location, sorted
-    uint16_t start[kCondCap + 1];       // first key of each distinct feature
+template <typename T, uint32_t CAP, uint32_t BINS>
+struct SliceLds {
+    T key[CAP];                   // grouped by bin
+    uint16_t bin[sizeof(T) == 8 ? CAP : 1];   // of each key (write pass)
+    uint32_t cnt[BINS];           // per bin: entries, then cursors or features
+    uint16_t start[BINS + 1];     // first key of each bin
+    uint16_t longs[kCondMaxLong]; // bins of more than kCondLong keys
     uint32_t wsum[kCondWaves];
-    uint32_t n, nfeat, err;
-    uint32_t end_bucket;                // offset of the first non-full bucket from b1 - 1
-    unsigned long long vsum;
+    uint32_t tail, n_long, sum[2];
 };
-
-__device__ __forceinline__ bool bucket_full(const unsigned long long* table, uint64_t b) {
-    return table[b * kSlots + (kSlots - 1)] != kEmpty;
-}
 
 // Exclusive prefix of one u32 per thread over the workgroup.
 __device__ __forceinline__ uint32_t cond_scan(uint32_t v, uint32_t* wsum, uint32_t& total) {
@@ -57,209 +87,474 @@ __device__ __forceinline__ uint32_t cond_scan(uint32_t v, uint32_t* wsum, uint32
     return base + x - v;
 }
 
-// Entries homed in slice z (buckets [b0, b1)) into L.key, sorted, and the
-// first key of every distinct feature into L.start (L.start[nfeat] = n).
-// Returns false (and sets L.err) if the slice holds more than kCondCap.
-__device__ bool gather_slice(const CondArgs& c, uint32_t z, CondLds& L) {
-    const uint32_t tid = threadIdx.x;
-    const uint64_t b0 = (uint64_t)z << kCondSliceShift;
-    const uint64_t b1 = b0 + (1ull << kCondSliceShift) < c.nb ? b0 + (1ull << kCondSliceShift)
-                                                              : c.nb;
-    if (tid == 0) {
-        L.n = 0;
-        L.err = 0;
-        L.end_bucket = 0xFFFFFFFFu;
+// Buckets past the slice's last one that its chains run on into: up to the
+// first bucket that is not full at or after b1 - 1 (the table wraps around).
+// One wave; kNone if no bucket of the table has a free slot (not a valid table).
+__device__ __forceinline__ uint32_t tail_buckets(const CondArgs& c, uint32_t b1) {
+    const uint32_t lane = (uint32_t)lane_id(), nb = (uint32_t)c.nb;
+    // chains are short: eight buckets first, then 64 at a time
+    for (uint64_t base = 0, width = 8; base < nb; base += width, width = kWave) {
+        const uint64_t o = base + lane;
+        const uint64_t b = (uint64_t)b1 - 1 + o;
+        bool open = false;
+        if (lane < width && o < nb)
+            open = c.table[(b < nb ? b : b - nb) * kSlots + (kSlots - 1)] == kEmpty;
+        const uint64_t m = ballot(open);
+        if (m) return min((uint32_t)(base + __builtin_ctzll(m)), nb - kCondBuckets);
     }
-    __syncthreads();
-    // chains of features homed in the slice end at the first bucket that is
-    // not full at or after b1 - 1 (buckets wrap around the table's end)
-    // (chains are short: the first 64 buckets are tried first)
-    for (uint64_t base = 0, width = kWave; base < c.nb; base += width, width = kCondThreads) {
-        const uint64_t o = base + tid;
-        if (tid < width && o < c.nb && !bucket_full(c.table, (b1 - 1 + o) % c.nb))
-            atomicMin(&L.end_bucket, (uint32_t)o);
-        __syncthreads();
-        if (L.end_bucket != 0xFFFFFFFFu) break;
-        __syncthreads();
-    }
-    const uint32_t end = L.end_bucket;
-    __syncthreads();
-    if (end == 0xFFFFFFFFu) return false;   // no bucket with a free slot: not a valid table
-    // buckets [b0, b1 - 1 + end], each once
-    uint64_t n_scan = (b1 - b0) + end;
-    if (n_scan > c.nb) n_scan = c.nb;
-    const uint64_t n_slots = n_scan * kSlots;
-    for (uint64_t i = tid; i < n_slots; i += kCondThreads) {
-        const uint64_t b = (b0 + i / kSlots) % c.nb;
-        const unsigned long long e = c.table[b * kSlots + i % kSlots];
-        if (!live_entry(e)) continue;
-        const uint64_t h = home_bucket((uint32_t)(e >> 32), c.nb);
-        if (h < b0 || h >= b1) continue;
-        const uint32_t pos = atomicAdd(&L.n, 1u);
-        if (pos < kCondCap) L.key[pos] = e;
-        else L.err = 1;
-    }
-    __syncthreads();
-    const bool bad = L.err != 0;
-    const uint32_t n = L.n;
-    __syncthreads();   // every thread has read them before the next slice resets them
-    if (bad) return false;
-    // bitonic sort of key[0, P), P the power of two >= n, padded with the largest key
-    uint32_t P = 1;
-    while (P < n) P <<= 1;
-    for (uint32_t i = n + tid; i < P; i += kCondThreads) L.key[i] = ~0ull;
-    __syncthreads();
-    for (uint32_t size = 2; size <= P; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-            for (uint32_t x = tid; x < P / 2; x += kCondThreads) {
-                const uint32_t i = (x / stride) * 2 * stride + (x % stride), j = i + stride;
-                const bool asc = (i & size) == 0;
-                const unsigned long long a = L.key[i], b = L.key[j];
-                if ((a > b) == asc) {
-                    L.key[i] = b;
-                    L.key[j] = a;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    // distinct features: a chunk of consecutive keys per thread
-    const uint32_t per = (n + kCondThreads - 1) / kCondThreads;
-    const uint32_t i0 = min(n, tid * per), i1 = min(n, i0 + per);
-    uint32_t cnt = 0;
-    for (uint32_t i = i0; i < i1; ++i)
-        cnt += (i == 0 || (L.key[i] >> 32) != (L.key[i - 1] >> 32)) ? 1u : 0u;
-    uint32_t total;
-    uint32_t r = cond_scan(cnt, L.wsum, total);
-    for (uint32_t i = i0; i < i1; ++i)
-        if (i == 0 || (L.key[i] >> 32) != (L.key[i - 1] >> 32)) L.start[r++] = (uint16_t)i;
-    if (tid == 0) {
-        L.nfeat = total;
-        L.start[total] = (uint16_t)n;
-    }
-    __syncthreads();
-    return true;
+    return kNone;
 }
 
-// Count pass: distinct features and run values of every slice.
-__global__ __launch_bounds__(kCondThreads) void k_condense_count(CondArgs c) {
-    __shared__ CondLds L;
+// The entries homed in slice z into L.key, grouped by bin (bin_of(h2(feature)),
+// below nbins <= BINS): bin r holds key[start[r], start[r + 1]). Returns their
+// number; more than CAP (then nothing is stored), or kNone for a table without
+// a free slot. Called by the whole workgroup, which must be done with L.
+template <typename T, uint32_t CAP, uint32_t BINS, typename BinOf>
+__device__ uint32_t group_slice(const CondArgs& c, uint32_t z, SliceLds<T, CAP, BINS>& L,
+                                uint32_t nbins, BinOf bin_of) {
+    const uint32_t nb = (uint32_t)c.nb;
+    uint32_t tid = threadIdx.x;           // per-thread indices anew for each slice (not
+    asm volatile("" : "+v"(tid));         // held in registers across the slices)
+    const uint32_t b0 = z << kCondSliceShift, b1 = b0 + kCondBuckets;
+    const unsigned long long* const tab = c.table + (uint64_t)b0 * kSlots;
+    for (uint32_t r = tid; r < nbins; r += kCondThreads) L.cnt[r] = 0u;
+    if (tid == 0) L.n_long = 0u;
+    // the slice's own slots, all loads in flight together
+    unsigned long long e[kCondHeld];
+#pragma unroll
+    for (int j = 0; j < kCondHeld; ++j) e[j] = tab[(uint32_t)j * kCondThreads + tid];
+    if (tid < kWave) {
+        const uint32_t t = tail_buckets(c, b1);
+        if (tid == 0) L.tail = t;
+    }
+    __syncthreads();
+    const uint32_t tail = L.tail;
+    if (tail == kNone) return kNone;
+    // bin << 16 | rank within the bin of an entry homed in the slice, else kNone
+    auto place = [&](unsigned long long x) -> uint32_t {
+        const uint32_t h = h2((uint32_t)(x >> 32));
+        if (!live_entry(x) || __umulhi(h, nb) - b0 >= kCondBuckets) return kNone;
+        const uint32_t r = bin_of(h);
+        return (r << 16) | atomicAdd(&L.cnt[r], 1u);
+    };
+    auto tail_slot = [&](uint32_t i) -> unsigned long long {
+        const uint64_t b = (uint64_t)b1 + i / kSlots;
+        return c.table[(b < nb ? b : b - nb) * kSlots + i % kSlots];
+    };
+    uint32_t at[kCondHeld], at_tail = kNone;
+#pragma unroll
+    for (int j = 0; j < kCondHeld; ++j) at[j] = place(e[j]);
+    // tails of up to kCondThreads slots are held like the slice's own; of
+    // longer ones every entry is read again for its place
+    const uint32_t n_tail = tail * kSlots;
+    const bool again = n_tail > (uint32_t)kCondThreads;
+    unsigned long long et = kEmpty;
+    if (tid < n_tail) {
+        et = tail_slot(tid);
+        at_tail = place(et);
+    }
+    for (uint32_t i = tid + kCondThreads; i < n_tail; i += kCondThreads) (void)place(tail_slot(i));
+    __syncthreads();
+    constexpr uint32_t PER = (BINS + kCondThreads - 1) / kCondThreads;
+    uint32_t own[PER], sum = 0, n;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t r = tid * PER + k;
+        own[k] = r < nbins ? L.cnt[r] : 0u;
+        sum += own[k];
+    }
+    uint32_t run = cond_scan(sum, L.wsum, n);
+    if (n > CAP) return n;
+#pragma unroll
+    for (uint32_t k = 0; k < PER; ++k) {
+        const uint32_t r = tid * PER + k;
+        if (r < nbins) {
+            L.start[r] = (uint16_t)run;
+            L.cnt[r] = run;            // cursors, where the entries are read again
+            if (own[k] > kCondLong) L.longs[atomicAdd(&L.n_long, 1u)] = (uint16_t)r;
+            run += own[k];
+        }
+    }
+    if (tid == 0) L.start[nbins] = (uint16_t)n;
+    __syncthreads();
+    auto put = [&](unsigned long long x, uint32_t r, uint32_t pos) {
+        if constexpr (sizeof(T) == 8) {
+            L.key[pos] = x;
+            L.bin[pos] = (uint16_t)r;
+        } else {
+            L.key[pos] = (uint32_t)(x >> 32);
+        }
+    };
+    if (!again) {
+#pragma unroll
+        for (int j = 0; j < kCondHeld; ++j)
+            if (at[j] != kNone)
+                put(e[j], at[j] >> 16, L.start[at[j] >> 16] + (at[j] & 0xFFFFu));
+        if (at_tail != kNone)
+            put(et, at_tail >> 16, L.start[at_tail >> 16] + (at_tail & 0xFFFFu));
+    } else {
+        auto put_again = [&](unsigned long long x) {
+            const uint32_t h = h2((uint32_t)(x >> 32));
+            if (live_entry(x) && __umulhi(h, nb) - b0 < kCondBuckets) {
+                const uint32_t r = bin_of(h);
+                put(x, r, atomicAdd(&L.cnt[r], 1u));
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < kCondHeld; ++j) put_again(e[j]);
+        for (uint32_t i = tid; i < n_tail; i += kCondThreads) put_again(tail_slot(i));
+    }
+    __syncthreads();
+    // long bins: bitonic sort with every comparison ascending (entries past the
+    // end count as largest and never move)
+    for (uint32_t x = 0; x < L.n_long; ++x) {
+        const uint32_t r = L.longs[x];
+        T* const k = L.key + L.start[r];
+        const uint32_t m = (uint32_t)L.start[r + 1] - L.start[r];
+        uint32_t P = 1;
+        while (P < m) P <<= 1;
+        for (uint32_t size = 2; size <= P; size <<= 1) {
+            for (uint32_t st = size >> 1; st > 0; st >>= 1) {
+                for (uint32_t y = tid; y < P / 2; y += kCondThreads) {
+                    const uint32_t o = y & (st - 1u), i = 2u * (y - o) + o;
+                    // the first step of a size pairs mirrored places of a block
+                    const uint32_t j = st == size >> 1 ? 2u * (y - o) + size - 1u - o : i + st;
+                    if (j < m && k[j] < k[i]) {
+                        const T v = k[i];
+                        k[i] = k[j];
+                        k[j] = v;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+    }
+    return n;
+}
+
+// First position in the sorted keys [lo, hi) whose feature is at least f (over:
+// above f).
+template <typename T>
+__device__ __forceinline__ uint32_t feature_bound(const T* key, uint32_t lo, uint32_t hi,
+                                                  uint32_t f, bool over) {
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        const uint32_t g = (uint32_t)(key[mid] >> (8 * sizeof(T) - 32));
+        if (g < f || (over && g == f)) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// Count pass: entries, distinct features and run values of every slice.
+__global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_condense_count(CondArgs c) {
+    __shared__ SliceLds<uint32_t, kCondCap, kCondCountBins> L;
+    const uint32_t tid = threadIdx.x, nbins = kCondBuckets << c.split_t;
+    const uint32_t nbs = (uint32_t)c.nb << c.split_t;
     for (uint32_t z = blockIdx.x; z < c.n_slices; z += gridDim.x) {
-        if (!gather_slice(c, z, L)) {
-            if (threadIdx.x == 0) atomicOr(&c.err[0], 1u);
-            continue;
-        }
-        if (threadIdx.x == 0) L.vsum = 0;
         __syncthreads();
-        unsigned long long v = 0;
-        for (uint32_t f = threadIdx.x; f < L.nfeat; f += kCondThreads) {
-            const uint32_t n = (uint32_t)L.start[f + 1] - L.start[f];
-            if (n > kCondInline) v += n;
-        }
-        if (v) atomicAdd(&L.vsum, v);
+        const uint32_t r0 = z * nbins;
+        const uint32_t n = group_slice<uint32_t, kCondCap, kCondCountBins>(
+            c, z, L, nbins, [=](uint32_t h) { return __umulhi(h, nbs) - r0; });
+        if (tid < 2) L.sum[tid] = 0u;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            c.slice_feats[z] = L.nfeat;
-            c.slice_vals[z] = L.vsum;
+        uint32_t feats = 0, vals = 0;
+        for (uint32_t p = tid; p < (n <= kCondCap ? n : 0u); p += kCondThreads) {
+            const uint32_t f = L.key[p];
+            const uint32_t r = __umulhi(h2(f), nbs) - r0;
+            const uint32_t s0 = L.start[r], s1 = L.start[r + 1];
+            uint32_t same = 0, first = p;
+            if (s1 - s0 <= kCondLong) {
+                for (uint32_t q = s1; q-- > s0;)
+                    if (L.key[q] == f) {
+                        same += 1u;
+                        first = q;
+                    }
+            } else {
+                first = feature_bound(L.key, s0, s1, f, false);
+                same = feature_bound(L.key, s0, s1, f, true) - first;
+            }
+            feats += first == p ? 1u : 0u;
+            vals += same > kCondInline ? 1u : 0u;
+        }
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) {
+            feats += shfl_xor(feats, m);
+            vals += shfl_xor(vals, m);
+        }
+        if (lane_id() == 0) {
+            atomicAdd(&L.sum[0], feats);
+            atomicAdd(&L.sum[1], vals);
         }
         __syncthreads();
+        if (tid == 0) {
+            c.slice_cnt[z] = ((unsigned long long)n << 32) | L.sum[0];
+            c.slice_vals[z] = L.sum[1];
+        }
     }
 }
 
 // Exclusive prefix of slice_vals in place (slice_vals[n_slices] = total) and
-// the total of slice_feats, by one workgroup of 1024 threads.
-__global__ __launch_bounds__(kCondThreads) void k_condense_scan(CondArgs c,
-                                                                unsigned long long* total_feats) {
-    __shared__ unsigned long long ws[kCondWaves], wf[kCondWaves];
+// the totals (CondResult), by one workgroup in tiles of four slices a thread.
+constexpr int kCondScanThreads = 1024;
+__global__ __launch_bounds__(kCondScanThreads) void k_condense_scan(CondArgs c) {
+    constexpr uint32_t W = kCondScanThreads / kWave, U = 4;
+    __shared__ unsigned long long ws[W], wf[W], wn[W];
+    __shared__ uint32_t wm[W];
     const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6, n = c.n_slices;
-    const uint32_t per = (n + kCondThreads - 1) / kCondThreads;
-    const uint32_t i0 = min(n, t * per), i1 = min(n, i0 + per);
-    unsigned long long sv = 0, sf = 0;
-    for (uint32_t i = i0; i < i1; ++i) {
-        sv += c.slice_vals[i];
-        sf += c.slice_feats[i];
-    }
-    unsigned long long x = sv;
+    unsigned long long base = 0, feats = 0, pairs = 0;
+    uint32_t most = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += kCondScanThreads * U) {
+        unsigned long long v[U], sum = 0;
 #pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int src = lane >= (uint32_t)d ? (int)lane - d : (int)lane;
-        const uint32_t lo = shfl_idx((uint32_t)x, src), hi = shfl_idx((uint32_t)(x >> 32), src);
-        if (lane >= (uint32_t)d) x += ((unsigned long long)hi << 32) | lo;
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = i0 + t * U + u;
+            v[u] = i < n ? c.slice_vals[i] : 0ull;
+            const unsigned long long x = i < n ? c.slice_cnt[i] : 0ull;
+            sum += v[u];
+            feats += (uint32_t)x;
+            pairs += x >> 32;
+            most = max(most, (uint32_t)(x >> 32));
+        }
+        unsigned long long x = sum;   // inclusive wave scan
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int src = lane >= (uint32_t)d ? (int)lane - d : (int)lane;
+            const uint32_t lo = shfl_idx((uint32_t)x, src), hi = shfl_idx((uint32_t)(x >> 32), src);
+            if (lane >= (uint32_t)d) x += ((unsigned long long)hi << 32) | lo;
+        }
+        __syncthreads();
+        if (lane == kWave - 1) ws[w] = x;
+        __syncthreads();
+        unsigned long long run = base + x - sum;
+        for (uint32_t k = 0; k < W; ++k) {
+            if (k < w) run += ws[k];
+            base += ws[k];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t i = i0 + t * U + u;
+            if (i < n) c.slice_vals[i] = run;
+            run += v[u];
+        }
     }
 #pragma unroll
     for (int m = 1; m < kWave; m <<= 1) {
-        const uint32_t lo = shfl_xor((uint32_t)sf, m), hi = shfl_xor((uint32_t)(sf >> 32), m);
-        sf += ((unsigned long long)hi << 32) | lo;
+        feats += ((unsigned long long)shfl_xor((uint32_t)(feats >> 32), m) << 32) +
+                 shfl_xor((uint32_t)feats, m);
+        pairs += ((unsigned long long)shfl_xor((uint32_t)(pairs >> 32), m) << 32) +
+                 shfl_xor((uint32_t)pairs, m);
+        most = max(most, shfl_xor(most, m));
     }
-    if (lane == kWave - 1) ws[w] = x;
-    if (lane == 0) wf[w] = sf;
+    if (lane == 0) {
+        wf[w] = feats;
+        wn[w] = pairs;
+        wm[w] = most;
+    }
     __syncthreads();
-    unsigned long long base = 0, total = 0, tf = 0;
-    for (uint32_t i = 0; i < kCondWaves; ++i) {
-        if (i < w) base += ws[i];
-        total += ws[i];
-        tf += wf[i];
-    }
-    unsigned long long run = base + x - sv;
-    for (uint32_t i = i0; i < i1; ++i) {
-        const unsigned long long v = c.slice_vals[i];
-        c.slice_vals[i] = run;
-        run += v;
-    }
     if (t == 0) {
-        c.slice_vals[n] = total;
-        *total_feats = tf;
+        CondResult r{};
+        for (uint32_t k = 0; k < W; ++k) {
+            r.feats += wf[k];
+            r.pairs += wn[k];
+            r.most = max(r.most, wm[k]);
+        }
+        r.vals = base;
+        c.slice_vals[n] = base;
+        *c.res = r;
     }
 }
 
-// Write pass: runs at the slice's value prefix (features in ascending order),
-// one index entry per feature.
-__global__ __launch_bounds__(kCondThreads) void k_condense_write(CondArgs c) {
-    __shared__ CondLds L;
+// Write pass: the slice's runs at its value prefix, its index lines whole.
+// Slices of more than CAP entries, and in the kCondCap form those of at most
+// kCondMid, are left to the other form.
+template <uint32_t CAP>
+__global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(CAP <= kCondMid ? 6 : 2))) void k_condense_write(CondArgs c) {
+    constexpr uint32_t PER = (CAP + kCondThreads - 1) / kCondThreads;
+    constexpr uint32_t BPER = kCondMaxPer / kCondThreads;
+    __shared__ SliceLds<unsigned long long, CAP, kCondWriteBins> L;
+    __shared__ uint16_t voff[CAP];           // of a feature's first entry: offset of its run
+    __shared__ uint16_t Te[kCondMaxPer];     // features homed below index bucket r
+    __shared__ uint16_t Tp[kCondMaxPer];     // features placed in index buckets <= r
+    __shared__ int wA[kCondWaves], wD[kCondWaves];
+    __shared__ uint32_t vcur;
+    const uint32_t R = c.per_slice;
+    const int kLow = -(1 << 30);
+    uint4* const idx = reinterpret_cast<uint4*>(c.idx);
     for (uint32_t z = blockIdx.x; z < c.n_slices; z += gridDim.x) {
-        if (!gather_slice(c, z, L)) continue;   // reported by the count pass
-        // value offsets of the features' runs: a chunk of features per thread
-        const uint32_t nf = L.nfeat;
-        const uint32_t per = (nf + kCondThreads - 1) / kCondThreads;
-        const uint32_t f0 = min(nf, threadIdx.x * per), f1 = min(nf, f0 + per);
-        uint32_t own = 0;
-        for (uint32_t f = f0; f < f1; ++f) {
-            const uint32_t n = (uint32_t)L.start[f + 1] - L.start[f];
-            if (n > kCondInline) own += n;
-        }
-        uint32_t total;
-        uint64_t off = c.slice_vals[z] + cond_scan(own, L.wsum, total);
-        for (uint32_t f = f0; f < f1; ++f) {
-            const uint32_t s = L.start[f], n = (uint32_t)L.start[f + 1] - s;
-            const uint32_t feat = (uint32_t)(L.key[s] >> 32);
-            uint4 e;
-            e.x = feat;
-            e.y = n;
-            if (n > kCondInline) {
-                for (uint32_t i = 0; i < n; ++i) c.val[off + i] = (uint32_t)L.key[s + i];
-                e.z = (uint32_t)off;
-                e.w = (uint32_t)(off >> 32);
-                off += n;
-            } else {
-                e.z = (uint32_t)L.key[s];
-                e.w = n > 1 ? (uint32_t)L.key[s + 1] : 0u;
-            }
-            // claim an entry: the home bucket's next one, or the next bucket's
-            uint64_t b = home_bucket(feat, c.nbc);
-            bool placed = false;
-            for (uint64_t d = 0; d < c.nbc && !placed; ++d) {
-                if (c.fill[b] < kCondEntries) {
-                    const uint32_t p = atomicAdd(&c.fill[b], 1u);
-                    if (p < kCondEntries) {
-                        reinterpret_cast<uint4*>(c.idx)[b * kCondEntries + p] = e;
-                        placed = true;
+        const uint32_t cnt = (uint32_t)(c.slice_cnt[z] >> 32);
+        if (CAP == kCondMid ? cnt > kCondMid : cnt <= kCondMid) continue;
+        __syncthreads();
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const uint32_t lane = tid & 63u, w = tid >> 6;
+        const uint32_t sh = c.split_c, nbins = R << sh;
+        const uint32_t nbs = (uint32_t)c.nbc << sh, r0 = z * nbins;
+        const uint32_t n = group_slice<unsigned long long, CAP, kCondWriteBins>(
+            c, z, L, nbins, [=](uint32_t h) { return __umulhi(h, nbs) - r0; });
+        for (uint32_t r = tid; r < R; r += kCondThreads) L.cnt[r] = 0u;   // features per bucket
+        if (tid == 0) vcur = 0u;
+        __syncthreads();
+        // each entry: its rank among its feature's locations, the feature's
+        // first entry, the number of its locations, and for the first entry the
+        // feature's number in its bucket and its second location
+        uint32_t rank_first[PER], num_same[PER], second[PER];
+#pragma unroll
+        for (uint32_t k = 0; k < PER; ++k) {
+            const uint32_t p = k * kCondThreads + tid;
+            rank_first[k] = num_same[k] = second[k] = 0u;
+            if (p >= n) continue;
+            const unsigned long long e = L.key[p];
+            const uint32_t f = (uint32_t)(e >> 32), loc = (uint32_t)e;
+            const uint32_t r = L.bin[p], s0 = L.start[r], s1 = L.start[r + 1];
+            uint32_t s = 0, rank = 0, first = p, least = loc, next = 0u;
+            if (s1 - s0 <= kCondLong) {
+                for (uint32_t q = s0; q < s1; ++q) {
+                    const unsigned long long x = L.key[q];
+                    if ((uint32_t)(x >> 32) != f) continue;
+                    const uint32_t l = (uint32_t)x;
+                    s += 1u;
+                    if (l < loc || (l == loc && q < p)) rank += 1u;
+                    if (l < least || (l == least && q < first)) {
+                        least = l;
+                        first = q;
                     }
+                    if (q != p) next = l;    // the other location of two
                 }
-                b = b + 1 == c.nbc ? 0 : b + 1;
+            } else {
+                first = feature_bound(L.key, s0, s1, f, false);
+                s = feature_bound(L.key, s0, s1, f, true) - first;
+                rank = p - first;
+                next = s > 1u ? (uint32_t)L.key[first + 1u] : 0u;
             }
-            if (!placed) atomicOr(&c.err[1], 1u);
+            num_same[k] = s;
+            rank_first[k] = (rank << 16) | first;
+            if (rank == 0u) {
+                num_same[k] |= atomicAdd(&L.cnt[r >> sh], 1u) << 16;
+                second[k] = next;
+                if (s > kCondInline) voff[p] = (uint16_t)atomicAdd(&vcur, s);
+            }
         }
         __syncthreads();
+        // placement of the features: carry(r) = max(0, carry(r - 1) + features
+        // homed at r - entries of a bucket), buckets <= r hold the first
+        // N(r) - carry(r) features in home order
+        uint32_t S = 0;
+        int A = kLow, D = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < BPER; ++k) {
+            const uint32_t r = tid * BPER + k;
+            if (r >= R) break;
+            const int d = (int)L.cnt[r] - (int)kCondEntries;
+            S += L.cnt[r];
+            A = max(0, A + d);
+            D += d;
+        }
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int src = lane >= (uint32_t)d ? (int)lane - d : (int)lane;
+            const uint32_t pS = shfl_idx(S, src);
+            const int pA = (int)shfl_idx((uint32_t)A, src), pD = (int)shfl_idx((uint32_t)D, src);
+            if (lane >= (uint32_t)d) {
+                S += pS;
+                A = max(A, pA + D);
+                D += pD;
+            }
+        }
+        const int up = lane ? (int)lane - 1 : 0;
+        uint32_t eS = shfl_idx(S, up);
+        int eA = (int)shfl_idx((uint32_t)A, up), eD = (int)shfl_idx((uint32_t)D, up);
+        if (lane == 0) {
+            eS = 0;
+            eA = kLow;
+            eD = 0;
+        }
+        if (lane == kWave - 1) {
+            L.wsum[w] = S;
+            wA[w] = A;
+            wD[w] = D;
+        }
+        __syncthreads();
+        uint32_t PS = 0;
+        int PA = kLow, PD = 0;
+        for (uint32_t i = 0; i < w; ++i) {
+            PS += L.wsum[i];
+            PA = max(wA[i], PA + wD[i]);
+            PD += wD[i];
+        }
+        uint32_t run = PS + eS;
+        int carry = max(0, max(max(eA, PA + eD), PD + eD));
+#pragma unroll
+        for (uint32_t k = 0; k < BPER; ++k) {
+            const uint32_t r = tid * BPER + k;
+            if (r >= R) break;
+            const uint32_t nf = L.cnt[r];
+            Te[r] = (uint16_t)run;
+            run += nf;
+            carry = max(0, carry + (int)nf - (int)kCondEntries);
+            Tp[r] = (uint16_t)(run - (uint32_t)carry);
+        }
+        __syncthreads();
+        const uint32_t placed = Tp[R - 1];
+        const uint64_t v0 = c.slice_vals[z];
+        uint4* const lines = idx + (uint64_t)z * R * kCondEntries;
+#pragma unroll
+        for (uint32_t k = 0; k < PER; ++k) {
+            const uint32_t same = num_same[k] & 0xFFFFu;
+            if (same == 0u) continue;
+            const uint32_t p = k * kCondThreads + tid;
+            const unsigned long long e = L.key[p];
+            const uint32_t first = rank_first[k] & 0xFFFFu, rank = rank_first[k] >> 16;
+            const bool run_of = same > kCondInline;
+            const uint64_t off = v0 + voff[first];
+            if (run_of) c.val[off + rank] = (uint32_t)e;
+            if (rank != 0u) continue;
+            const uint32_t f = (uint32_t)(e >> 32);
+            uint4 x;
+            x.x = f;
+            x.y = same;
+            x.z = run_of ? (uint32_t)off : (uint32_t)e;
+            x.w = run_of ? (uint32_t)(off >> 32) : same == 2u ? second[k] : 0u;
+            uint32_t b = L.bin[p] >> sh;
+            const uint32_t j = Te[b] + (num_same[k] >> 16);
+            if (j >= placed) {             // carried past the slice's index buckets
+                const unsigned long long d = atomicAdd(&c.res->deferred, 1ull);
+                if (d < c.defer_cap) c.defer[d] = x;
+                continue;
+            }
+            while (j >= Tp[b]) b += 1u;
+            lines[b * kCondEntries + (j - (b ? Tp[b - 1u] : 0u))] = x;
+        }
+        for (uint32_t i = tid; i < R * kCondEntries; i += kCondThreads) {   // free entries
+            const uint32_t b = i / kCondEntries;
+            if (i % kCondEntries >= (uint32_t)Tp[b] - (b ? Tp[b - 1u] : 0u))
+                lines[i] = make_uint4(0u, 0u, 0u, 0u);
+        }
+    }
+}
+
+// Features carried past their slice's index buckets: each claims the first free
+// entry from its home bucket on (feature and count by one 64-bit exchange).
+__global__ __launch_bounds__(256) void k_condense_defer(CondArgs c) {
+    const unsigned long long n = min(c.res->deferred, (unsigned long long)c.defer_cap);
+    for (unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (unsigned long long)gridDim.x * blockDim.x) {
+        const uint4 x = c.defer[i];
+        const unsigned long long tag = ((unsigned long long)x.y << 32) | x.x;
+        uint64_t b = home_bucket(x.x, c.nbc);
+        bool placed = false;
+        for (uint64_t d = 0; d < c.nbc && !placed; ++d) {
+            for (uint32_t p = 0; p < kCondEntries && !placed; ++p) {
+                unsigned long long* const e =
+                    reinterpret_cast<unsigned long long*>(c.idx) + (b * kCondEntries + p) * 2;
+                if ((*e >> 32) == 0ull && atomicCAS(e, 0ull, tag) == 0ull) {
+                    e[1] = ((unsigned long long)x.w << 32) | x.z;
+                    placed = true;
+                }
+            }
+            b = b + 1 == c.nbc ? 0 : b + 1;
+        }
+        if (!placed) c.res->failed = 1u;
     }
 }
 
@@ -285,53 +580,44 @@ __global__ __launch_bounds__(256) void k_condense_dump(const unsigned int* idx, 
     }
 }
 
-// Pairs held by the condensed layout: the sum of its entries' counts, one
-// atomic per wave.
-__global__ __launch_bounds__(256) void k_condense_pairs(const unsigned int* idx, uint64_t nbc,
-                                                        unsigned long long* total) {
-    const uint64_t n = nbc * kCondEntries;
-    unsigned long long sum = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (uint64_t)gridDim.x * blockDim.x)
-        sum += reinterpret_cast<const uint4*>(idx)[i].y;
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) {
-        const uint32_t lo = shfl_xor((uint32_t)sum, m), hi = shfl_xor((uint32_t)(sum >> 32), m);
-        sum += ((unsigned long long)hi << 32) | lo;
-    }
-    if (lane_id() == 0 && sum) atomicAdd(total, sum);
-}
-
 inline unsigned grid_cap(uint64_t items, unsigned max_blocks) {
     return (unsigned)(items < 1 ? 1 : items > max_blocks ? max_blocks : items);
 }
 
+// log2 of the bins per bucket: buckets << split stays below 2^32 and the bins
+// of a slice (per buckets) within `most`.
+uint32_t bin_split(uint64_t buckets, uint32_t per, uint32_t most) {
+    uint32_t s = 0;
+    while (s < kCondBinSplit && (buckets << (s + 1)) <= 0xFFFFFFFFull && (per << (s + 1)) <= most) ++s;
+    return s;
+}
+
 }  // namespace
 
-hipError_t launch_condense_count(const CondArgs& c, hipStream_t st) {
-    hipLaunchKernelGGL(k_condense_count, dim3(grid_cap(c.n_slices, 8192)), dim3(kCondThreads), 0,
+hipError_t launch_condense_count(CondArgs c, hipStream_t st) {
+    c.split_t = bin_split(c.nb, kCondBuckets, kCondCountBins);
+    hipLaunchKernelGGL(k_condense_count, dim3(grid_cap(c.n_slices, 1u << 20)), dim3(kCondThreads), 0,
                        st, c);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_condense_scan, dim3(1), dim3(kCondScanThreads), 0, st, c);
     return hipGetLastError();
 }
 
-hipError_t launch_condense_scan(const CondArgs& c, unsigned long long* total_feats,
-                                hipStream_t st) {
-    hipLaunchKernelGGL(k_condense_scan, dim3(1), dim3(kCondThreads), 0, st, c, total_feats);
-    return hipGetLastError();
-}
-
-hipError_t launch_condense_write(const CondArgs& c, hipStream_t st) {
-    hipLaunchKernelGGL(k_condense_write, dim3(grid_cap(c.n_slices, 8192)), dim3(kCondThreads), 0,
-                       st, c);
-    return hipGetLastError();
-}
-
-hipError_t launch_condense_pairs(const unsigned int* idx, uint64_t nbc, unsigned long long* total,
-                                 hipStream_t st) {
-    if (nbc == 0) return hipSuccess;
-    const uint64_t n = nbc * kCondEntries;
-    hipLaunchKernelGGL(k_condense_pairs, dim3(grid_cap((n + 255) / 256, 16384)), dim3(256), 0, st,
-                       idx, nbc, total);
+hipError_t launch_condense_write(CondArgs c, uint32_t most, hipStream_t st) {
+    c.split_c = bin_split(c.nbc, c.per_slice, kCondWriteBins);
+    const dim3 grid(grid_cap(c.n_slices, 1u << 20)), blk(kCondThreads);
+    hipLaunchKernelGGL(k_condense_write<kCondMid>, grid, blk, 0, st, c);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && most > kCondMid) {
+        // few slices, if any: a small grid looks them up
+        hipLaunchKernelGGL(k_condense_write<kCondCap>, dim3(grid_cap(c.n_slices, 1024)), blk, 0, st,
+                           c);
+        e = hipGetLastError();
+    }
+    if (e != hipSuccess) return e;
+    // the count of deferred features is known on the device only
+    hipLaunchKernelGGL(k_condense_defer, dim3(64), dim3(256), 0, st, c);
     return hipGetLastError();
 }
 

@@ -219,18 +219,32 @@ constexpr uint32_t kCondInline = 2;
 constexpr uint32_t kCondSliceShift = 8;   // bucket-table buckets per conversion slice
 constexpr uint32_t kCondCap = 8192;       // entries homed in one slice (held in LDS)
 
+// Totals of a conversion (device, read back by the host).
+struct CondResult {
+    unsigned long long feats;      // distinct features
+    unsigned long long vals;       // values of all runs
+    unsigned long long pairs;      // live entries
+    unsigned long long deferred;   // features carried past their slice's index buckets
+    uint32_t most;                 // most entries homed in one slice (kNone: no free slot)
+    uint32_t failed;               // a deferred feature found no free entry
+};
+
 struct CondArgs {
     const unsigned long long* table;   // bucket table
-    uint64_t nb;
+    uint64_t nb;                       // a multiple of the slice size
     uint32_t n_slices;
-    uint64_t nbc;                      // index buckets
-    uint32_t* slice_feats;             // count pass: distinct features per slice
+    uint32_t per_slice;                // index buckets per slice
+    uint32_t split_t, split_c;         // log2 bins per table bucket (count pass) and per
+                                       // index bucket (write pass)
+    uint64_t nbc;                      // index buckets: n_slices * per_slice
+    unsigned long long* slice_cnt;     // per slice: entries << 32 | distinct features
     unsigned long long* slice_vals;    // count pass: run values per slice; then their
                                        // exclusive prefix (n_slices + 1)
     unsigned int* idx;                 // nbc * kCondEntries * 4 u32
-    uint32_t* fill;                    // entries claimed per index bucket
     uint32_t* val;                     // run values
-    uint32_t* err;                     // [0]: a slice over kCondCap entries, [1]: no free entry
+    uint4* defer;                      // entries of the deferred features
+    uint64_t defer_cap;
+    CondResult* res;
 };
 
 // Launchers (return hipError_t of the launch).
@@ -281,15 +295,10 @@ hipError_t launch_route(const QueryArgs& a, const RouteConfig& r, hipStream_t st
 hipError_t launch_classify_class(const QueryArgs& a, const ClassifyConfig& c, uint32_t cls,
                                  hipStream_t st);
 hipError_t launch_classify_huge(const QueryArgs& a, hipStream_t st);
-// Condensed layout build: the count pass (per slice), the prefix of the run
-// values, and the write pass (runs and index entries).
-hipError_t launch_condense_count(const CondArgs& c, hipStream_t st);
-hipError_t launch_condense_scan(const CondArgs& c, unsigned long long* total_feats,
-                                hipStream_t st);
-hipError_t launch_condense_write(const CondArgs& c, hipStream_t st);
-// Sum of the condensed entries' location counts into *total (which the caller zeroes).
-hipError_t launch_condense_pairs(const unsigned int* idx, uint64_t nbc, unsigned long long* total,
-                                 hipStream_t st);
+// Condensed layout build: the count pass (totals in c.res, prefix of the run
+// values), and the write pass (runs and index entries; most: the count pass's).
+hipError_t launch_condense_count(CondArgs c, hipStream_t st);
+hipError_t launch_condense_write(CondArgs c, uint32_t most, hipStream_t st);
 hipError_t launch_condense_dump(const unsigned int* idx, uint64_t nbc, const uint32_t* val,
                                 uint32_t lo, uint32_t hi, unsigned long long* out, uint64_t cap,
                                 unsigned long long* count, hipStream_t st);
