@@ -340,8 +340,9 @@ int mc_db_get_stats(mc_db* db, mc_db_stats* out);
  *   fail_after     1 = the next add reports MC_ERR_TABLE_FULL after all its
  *                  inserts ran, so that tests reach the rollback (the flag
  *                  clears itself);
- *   defer_entries  mc_db_condense: first size of its list of features that do
- *                  not fit their slice's index buckets.
+ *   defer_entries  most entries of the list for those that leave their slice
+ *                  when a table grows, and the first size of mc_db_condense's
+ *                  list of features that leave theirs.
  * MC_ERR_INVALID_ARG for slice_shift outside 4..13 (0 excepted). */
 typedef struct mc_insert_path {
     uint32_t global_insert;

@@ -323,13 +323,49 @@ int ensure_capacity(mc_db* db, uint64_t extra, hipStream_t st, bool defer_fill =
     if (rc) { (void)dev_free(t); return rc; }
     const bool grow = db->table != nullptr;
     if (grow && db->touched) {
-        HIP_TRY(launch_fill_u64(t, nb * kSlots, ~0ull, st));
-        HIP_TRY(launch_fill_u32(cnt, nb, 0u, st));
-        HIP_TRY(launch_fill_u64(db->counters, kNumBuildCounters, 0ull, st));
-        HIP_TRY(launch_rehash(db->table, db->nb, t, cnt, nb, db->counters, st));
         unsigned long long c[kNumBuildCounters];
-        HIP_TRY(hipMemcpyAsync(c, db->counters, sizeof c, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
+        bool done = false;
+        if (grow_slices_fit(db->nb, nb)) {
+            // entries that leave their slice: the idle build scratch holds them,
+            // or a list of a sixteenth of the entries (about 1 in 10,000 does
+            // at the default load; long chains of features with hundreds of
+            // locations may need more: then the entries are re-inserted)
+            unsigned long long* list = db->pairs;
+            uint64_t list_cap = std::min(db->pairs_cap, std::max<uint64_t>(db->slots_used, 4096));
+            const uint64_t least = db->slots_used / 16 + 4096;
+            bool have = list && list_cap >= std::min(least, db->slots_used);
+            unsigned long long* own = nullptr;
+            if (!have && dev_alloc(&own, least) == MC_OK) {
+                list = own;
+                list_cap = least;
+                have = true;
+            }
+            if (have) {
+                if (db->ipath.defer_entries) list_cap = std::min<uint64_t>(list_cap, db->ipath.defer_entries);
+                hipError_t e = launch_fill_u64(db->counters, kNumBuildCounters, 0ull, st);
+                if (e == hipSuccess)
+                    e = launch_grow_slices(db->table, db->nb, t, cnt, nb, db->counters, list,
+                                           list_cap, st);
+                if (e == hipSuccess)
+                    e = hipMemcpyAsync(c, db->counters, sizeof c, hipMemcpyDeviceToHost, st);
+                if (e == hipSuccess) e = hipStreamSynchronize(st);
+                (void)dev_free(own);
+                if (e != hipSuccess) {
+                    (void)dev_free(t);
+                    (void)dev_free(cnt);
+                    return fail(MC_ERR_HIP, "table growth: %s", hipGetErrorString(e));
+                }
+                done = c[kCntDefer] <= list_cap;
+            }
+        }
+        if (!done) {
+            HIP_TRY(launch_fill_u64(t, nb * kSlots, ~0ull, st));
+            HIP_TRY(launch_fill_u32(cnt, nb, 0u, st));
+            HIP_TRY(launch_fill_u64(db->counters, kNumBuildCounters, 0ull, st));
+            HIP_TRY(launch_rehash(db->table, db->nb, t, cnt, nb, db->counters, st));
+            HIP_TRY(hipMemcpyAsync(c, db->counters, sizeof c, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+        }
         if (c[kCntFull]) {
             (void)dev_free(t);
             (void)dev_free(cnt);

@@ -26,16 +26,15 @@
 // now 0.68 + 1.79 + 0.09 ms (5.9 GB moved by the write pass, 3.3 TB/s).
 #include "mc_device.hpp"
 #include "mc_internal.hpp"
+#include "mc_slices.hpp"
 
 namespace mc {
 
 namespace {
 
-constexpr int kCondThreads = 512;
-constexpr uint32_t kCondWaves = kCondThreads / kWave;
-constexpr uint32_t kCondBuckets = 1u << kCondSliceShift;
-constexpr uint32_t kCondSlots = kCondBuckets * kSlots;
-constexpr uint32_t kCondMaxPer = kCondSlots / 4;       // index buckets a slice at most
+constexpr int kCondThreads = kSliceThreads;
+constexpr uint32_t kCondBuckets = kSliceBuckets;
+constexpr uint32_t kCondMaxPer = kSliceSlots / 4;      // index buckets a slice at most
 // Bins of a slice: an entry is compared with the others of its bin, and a wave
 // takes as long as its largest bin, so buckets are split into finer bins by the
 // next bits of the home bucket's product (four a table bucket in the count
@@ -44,172 +43,36 @@ constexpr uint32_t kCondMaxPer = kCondSlots / 4;       // index buckets a slice 
 constexpr uint32_t kCondBinSplit = 2;                  // log2, most
 constexpr uint32_t kCondCountBins = kCondBuckets << kCondBinSplit;
 constexpr uint32_t kCondWriteBins = 2048;
-constexpr int kCondHeld = (int)(kCondSlots / kCondThreads);   // slots a thread holds
 // Entries of one slice in the write pass's usual form: a table at the default
 // load holds about 2,048 (at most 4,096 slots); slices beyond it take the
 // kCondCap form. 52 KB of LDS against 120 KB: three workgroups a CU, not one.
 constexpr uint32_t kCondMid = 2944;
-// A bucket with more entries is sorted by the workgroup: the comparisons of
-// every entry with all others of its bucket grow with the square.
+// A bin with more entries is sorted by the workgroup: the comparisons of every
+// entry with all others of its bin grow with the square.
 constexpr uint32_t kCondLong = 64;
 constexpr uint32_t kCondMaxLong = kCondCap / (kCondLong + 1) + 1;
 
-template <typename T, uint32_t CAP, uint32_t BINS>
-struct SliceLds {
-    T key[CAP];                   // grouped by bin
-    uint16_t bin[sizeof(T) == 8 ? CAP : 1];   // of each key (write pass)
-    uint32_t cnt[BINS];           // per bin: entries, then cursors or features
-    uint16_t start[BINS + 1];     // first key of each bin
-    uint16_t longs[kCondMaxLong]; // bins of more than kCondLong keys
-    uint32_t wsum[kCondWaves];
-    uint32_t tail, n_long, sum[2];
+struct LongBins {
+    uint32_t n;
+    uint16_t bin[kCondMaxLong];
 };
 
-// Exclusive prefix of one u32 per thread over the workgroup.
-__device__ __forceinline__ uint32_t cond_scan(uint32_t v, uint32_t* wsum, uint32_t& total) {
-    const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6;
-    uint32_t x = v;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t y = shfl_idx(x, lane >= (uint32_t)d ? (int)lane - d : (int)lane);
-        if (lane >= (uint32_t)d) x += y;
-    }
+// Sort the bins of more than kCondLong keys: a bitonic network with every
+// comparison ascending (keys past the end count as largest and never move).
+// Called by the whole workgroup after a barrier; ends with one.
+template <typename Lds>
+__device__ __forceinline__ void sort_long_bins(Lds& L, LongBins& B, uint32_t nbins) {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    if (tid == 0) B.n = 0u;
     __syncthreads();
-    if (lane == kWave - 1) wsum[w] = x;
+    for (uint32_t r = tid; r < nbins; r += kCondThreads)
+        if ((uint32_t)L.start[r + 1] - L.start[r] > kCondLong)
+            B.bin[atomicAdd(&B.n, 1u)] = (uint16_t)r;
     __syncthreads();
-    uint32_t base = 0;
-    total = 0;
-    for (uint32_t i = 0; i < kCondWaves; ++i) {
-        const uint32_t y = wsum[i];
-        if (i < w) base += y;
-        total += y;
-    }
-    return base + x - v;
-}
-
-// Buckets past the slice's last one that its chains run on into: up to the
-// first bucket that is not full at or after b1 - 1 (the table wraps around).
-// One wave; kNone if no bucket of the table has a free slot (not a valid table).
-__device__ __forceinline__ uint32_t tail_buckets(const CondArgs& c, uint32_t b1) {
-    const uint32_t lane = (uint32_t)lane_id(), nb = (uint32_t)c.nb;
-    // chains are short: eight buckets first, then 64 at a time
-    for (uint64_t base = 0, width = 8; base < nb; base += width, width = kWave) {
-        const uint64_t o = base + lane;
-        const uint64_t b = (uint64_t)b1 - 1 + o;
-        bool open = false;
-        if (lane < width && o < nb)
-            open = c.table[(b < nb ? b : b - nb) * kSlots + (kSlots - 1)] == kEmpty;
-        const uint64_t m = ballot(open);
-        if (m) return min((uint32_t)(base + __builtin_ctzll(m)), nb - kCondBuckets);
-    }
-    return kNone;
-}
-
-// The entries homed in slice z into L.key, grouped by bin (bin_of(h2(feature)),
-// below nbins <= BINS): bin r holds key[start[r], start[r + 1]). Returns their
-// number; more than CAP (then nothing is stored), or kNone for a table without
-// a free slot. Called by the whole workgroup, which must be done with L.
-template <typename T, uint32_t CAP, uint32_t BINS, typename BinOf>
-__device__ uint32_t group_slice(const CondArgs& c, uint32_t z, SliceLds<T, CAP, BINS>& L,
-                                uint32_t nbins, BinOf bin_of) {
-    const uint32_t nb = (uint32_t)c.nb;
-    uint32_t tid = threadIdx.x;           // per-thread indices anew for each slice (not
-    asm volatile("" : "+v"(tid));         // held in registers across the slices)
-    const uint32_t b0 = z << kCondSliceShift, b1 = b0 + kCondBuckets;
-    const unsigned long long* const tab = c.table + (uint64_t)b0 * kSlots;
-    for (uint32_t r = tid; r < nbins; r += kCondThreads) L.cnt[r] = 0u;
-    if (tid == 0) L.n_long = 0u;
-    // the slice's own slots, all loads in flight together
-    unsigned long long e[kCondHeld];
-#pragma unroll
-    for (int j = 0; j < kCondHeld; ++j) e[j] = tab[(uint32_t)j * kCondThreads + tid];
-    if (tid < kWave) {
-        const uint32_t t = tail_buckets(c, b1);
-        if (tid == 0) L.tail = t;
-    }
-    __syncthreads();
-    const uint32_t tail = L.tail;
-    if (tail == kNone) return kNone;
-    // bin << 16 | rank within the bin of an entry homed in the slice, else kNone
-    auto place = [&](unsigned long long x) -> uint32_t {
-        const uint32_t h = h2((uint32_t)(x >> 32));
-        if (!live_entry(x) || __umulhi(h, nb) - b0 >= kCondBuckets) return kNone;
-        const uint32_t r = bin_of(h);
-        return (r << 16) | atomicAdd(&L.cnt[r], 1u);
-    };
-    auto tail_slot = [&](uint32_t i) -> unsigned long long {
-        const uint64_t b = (uint64_t)b1 + i / kSlots;
-        return c.table[(b < nb ? b : b - nb) * kSlots + i % kSlots];
-    };
-    uint32_t at[kCondHeld], at_tail = kNone;
-#pragma unroll
-    for (int j = 0; j < kCondHeld; ++j) at[j] = place(e[j]);
-    // tails of up to kCondThreads slots are held like the slice's own; of
-    // longer ones every entry is read again for its place
-    const uint32_t n_tail = tail * kSlots;
-    const bool again = n_tail > (uint32_t)kCondThreads;
-    unsigned long long et = kEmpty;
-    if (tid < n_tail) {
-        et = tail_slot(tid);
-        at_tail = place(et);
-    }
-    for (uint32_t i = tid + kCondThreads; i < n_tail; i += kCondThreads) (void)place(tail_slot(i));
-    __syncthreads();
-    constexpr uint32_t PER = (BINS + kCondThreads - 1) / kCondThreads;
-    uint32_t own[PER], sum = 0, n;
-#pragma unroll
-    for (uint32_t k = 0; k < PER; ++k) {
-        const uint32_t r = tid * PER + k;
-        own[k] = r < nbins ? L.cnt[r] : 0u;
-        sum += own[k];
-    }
-    uint32_t run = cond_scan(sum, L.wsum, n);
-    if (n > CAP) return n;
-#pragma unroll
-    for (uint32_t k = 0; k < PER; ++k) {
-        const uint32_t r = tid * PER + k;
-        if (r < nbins) {
-            L.start[r] = (uint16_t)run;
-            L.cnt[r] = run;            // cursors, where the entries are read again
-            if (own[k] > kCondLong) L.longs[atomicAdd(&L.n_long, 1u)] = (uint16_t)r;
-            run += own[k];
-        }
-    }
-    if (tid == 0) L.start[nbins] = (uint16_t)n;
-    __syncthreads();
-    auto put = [&](unsigned long long x, uint32_t r, uint32_t pos) {
-        if constexpr (sizeof(T) == 8) {
-            L.key[pos] = x;
-            L.bin[pos] = (uint16_t)r;
-        } else {
-            L.key[pos] = (uint32_t)(x >> 32);
-        }
-    };
-    if (!again) {
-#pragma unroll
-        for (int j = 0; j < kCondHeld; ++j)
-            if (at[j] != kNone)
-                put(e[j], at[j] >> 16, L.start[at[j] >> 16] + (at[j] & 0xFFFFu));
-        if (at_tail != kNone)
-            put(et, at_tail >> 16, L.start[at_tail >> 16] + (at_tail & 0xFFFFu));
-    } else {
-        auto put_again = [&](unsigned long long x) {
-            const uint32_t h = h2((uint32_t)(x >> 32));
-            if (live_entry(x) && __umulhi(h, nb) - b0 < kCondBuckets) {
-                const uint32_t r = bin_of(h);
-                put(x, r, atomicAdd(&L.cnt[r], 1u));
-            }
-        };
-#pragma unroll
-        for (int j = 0; j < kCondHeld; ++j) put_again(e[j]);
-        for (uint32_t i = tid; i < n_tail; i += kCondThreads) put_again(tail_slot(i));
-    }
-    __syncthreads();
-    // long bins: bitonic sort with every comparison ascending (entries past the
-    // end count as largest and never move)
-    for (uint32_t x = 0; x < L.n_long; ++x) {
-        const uint32_t r = L.longs[x];
-        T* const k = L.key + L.start[r];
+    for (uint32_t x = 0; x < B.n; ++x) {
+        const uint32_t r = B.bin[x];
+        auto* const k = L.key + L.start[r];
         const uint32_t m = (uint32_t)L.start[r + 1] - L.start[r];
         uint32_t P = 1;
         while (P < m) P <<= 1;
@@ -220,7 +83,7 @@ __device__ uint32_t group_slice(const CondArgs& c, uint32_t z, SliceLds<T, CAP, 
                     // the first step of a size pairs mirrored places of a block
                     const uint32_t j = st == size >> 1 ? 2u * (y - o) + size - 1u - o : i + st;
                     if (j < m && k[j] < k[i]) {
-                        const T v = k[i];
+                        const auto v = k[i];
                         k[i] = k[j];
                         k[j] = v;
                     }
@@ -229,7 +92,6 @@ __device__ uint32_t group_slice(const CondArgs& c, uint32_t z, SliceLds<T, CAP, 
             }
         }
     }
-    return n;
 }
 
 // First position in the sorted keys [lo, hi) whose feature is at least f (over:
@@ -248,15 +110,18 @@ __device__ __forceinline__ uint32_t feature_bound(const T* key, uint32_t lo, uin
 
 // Count pass: entries, distinct features and run values of every slice.
 __global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_condense_count(CondArgs c) {
-    __shared__ SliceLds<uint32_t, kCondCap, kCondCountBins> L;
+    __shared__ SliceLds<uint32_t, kCondCap, kCondCountBins, false> L;
+    __shared__ LongBins B;
+    __shared__ uint32_t sum[2];
     const uint32_t tid = threadIdx.x, nbins = kCondBuckets << c.split_t;
     const uint32_t nbs = (uint32_t)c.nb << c.split_t;
     for (uint32_t z = blockIdx.x; z < c.n_slices; z += gridDim.x) {
         __syncthreads();
         const uint32_t r0 = z * nbins;
-        const uint32_t n = group_slice<uint32_t, kCondCap, kCondCountBins>(
-            c, z, L, nbins, [=](uint32_t h) { return __umulhi(h, nbs) - r0; });
-        if (tid < 2) L.sum[tid] = 0u;
+        const uint32_t n = group_slice(c.table, (uint32_t)c.nb, z << kCondSliceShift, kCondBuckets,
+                                       L, nbins, [=](uint32_t h) { return __umulhi(h, nbs) - r0; });
+        if (tid < 2) sum[tid] = 0u;
+        if (n <= kCondCap) sort_long_bins(L, B, nbins);
         __syncthreads();
         uint32_t feats = 0, vals = 0;
         for (uint32_t p = tid; p < (n <= kCondCap ? n : 0u); p += kCondThreads) {
@@ -283,13 +148,13 @@ __global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(8)
             vals += shfl_xor(vals, m);
         }
         if (lane_id() == 0) {
-            atomicAdd(&L.sum[0], feats);
-            atomicAdd(&L.sum[1], vals);
+            atomicAdd(&sum[0], feats);
+            atomicAdd(&sum[1], vals);
         }
         __syncthreads();
         if (tid == 0) {
-            c.slice_cnt[z] = ((unsigned long long)n << 32) | L.sum[0];
-            c.slice_vals[z] = L.sum[1];
+            c.slice_cnt[z] = ((unsigned long long)n << 32) | sum[0];
+            c.slice_vals[z] = sum[1];
         }
     }
 }
@@ -372,14 +237,13 @@ template <uint32_t CAP>
 __global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(CAP <= kCondMid ? 6 : 2))) void k_condense_write(CondArgs c) {
     constexpr uint32_t PER = (CAP + kCondThreads - 1) / kCondThreads;
     constexpr uint32_t BPER = kCondMaxPer / kCondThreads;
-    __shared__ SliceLds<unsigned long long, CAP, kCondWriteBins> L;
+    __shared__ SliceLds<unsigned long long, CAP, kCondWriteBins, true> L;
+    __shared__ LongBins B;
     __shared__ uint16_t voff[CAP];           // of a feature's first entry: offset of its run
     __shared__ uint16_t Te[kCondMaxPer];     // features homed below index bucket r
     __shared__ uint16_t Tp[kCondMaxPer];     // features placed in index buckets <= r
-    __shared__ int wA[kCondWaves], wD[kCondWaves];
     __shared__ uint32_t vcur;
     const uint32_t R = c.per_slice;
-    const int kLow = -(1 << 30);
     uint4* const idx = reinterpret_cast<uint4*>(c.idx);
     for (uint32_t z = blockIdx.x; z < c.n_slices; z += gridDim.x) {
         const uint32_t cnt = (uint32_t)(c.slice_cnt[z] >> 32);
@@ -387,11 +251,11 @@ __global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(CA
         __syncthreads();
         uint32_t tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        const uint32_t lane = tid & 63u, w = tid >> 6;
         const uint32_t sh = c.split_c, nbins = R << sh;
         const uint32_t nbs = (uint32_t)c.nbc << sh, r0 = z * nbins;
-        const uint32_t n = group_slice<unsigned long long, CAP, kCondWriteBins>(
-            c, z, L, nbins, [=](uint32_t h) { return __umulhi(h, nbs) - r0; });
+        const uint32_t n = group_slice(c.table, (uint32_t)c.nb, z << kCondSliceShift, kCondBuckets,
+                                       L, nbins, [=](uint32_t h) { return __umulhi(h, nbs) - r0; });
+        sort_long_bins(L, B, nbins);
         for (uint32_t r = tid; r < R; r += kCondThreads) L.cnt[r] = 0u;   // features per bucket
         if (tid == 0) vcur = 0u;
         __syncthreads();
@@ -436,65 +300,13 @@ __global__ __launch_bounds__(kCondThreads) __attribute__((amdgpu_waves_per_eu(CA
             }
         }
         __syncthreads();
-        // placement of the features: carry(r) = max(0, carry(r - 1) + features
-        // homed at r - entries of a bucket), buckets <= r hold the first
-        // N(r) - carry(r) features in home order
-        uint32_t S = 0;
-        int A = kLow, D = 0;
-#pragma unroll
-        for (uint32_t k = 0; k < BPER; ++k) {
-            const uint32_t r = tid * BPER + k;
-            if (r >= R) break;
-            const int d = (int)L.cnt[r] - (int)kCondEntries;
-            S += L.cnt[r];
-            A = max(0, A + d);
-            D += d;
-        }
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-            const int src = lane >= (uint32_t)d ? (int)lane - d : (int)lane;
-            const uint32_t pS = shfl_idx(S, src);
-            const int pA = (int)shfl_idx((uint32_t)A, src), pD = (int)shfl_idx((uint32_t)D, src);
-            if (lane >= (uint32_t)d) {
-                S += pS;
-                A = max(A, pA + D);
-                D += pD;
-            }
-        }
-        const int up = lane ? (int)lane - 1 : 0;
-        uint32_t eS = shfl_idx(S, up);
-        int eA = (int)shfl_idx((uint32_t)A, up), eD = (int)shfl_idx((uint32_t)D, up);
-        if (lane == 0) {
-            eS = 0;
-            eA = kLow;
-            eD = 0;
-        }
-        if (lane == kWave - 1) {
-            L.wsum[w] = S;
-            wA[w] = A;
-            wD[w] = D;
-        }
-        __syncthreads();
-        uint32_t PS = 0;
-        int PA = kLow, PD = 0;
-        for (uint32_t i = 0; i < w; ++i) {
-            PS += L.wsum[i];
-            PA = max(wA[i], PA + wD[i]);
-            PD += wD[i];
-        }
-        uint32_t run = PS + eS;
-        int carry = max(0, max(max(eA, PA + eD), PD + eD));
-#pragma unroll
-        for (uint32_t k = 0; k < BPER; ++k) {
-            const uint32_t r = tid * BPER + k;
-            if (r >= R) break;
-            const uint32_t nf = L.cnt[r];
-            Te[r] = (uint16_t)run;
-            run += nf;
-            carry = max(0, carry + (int)nf - (int)kCondEntries);
-            Tp[r] = (uint16_t)(run - (uint32_t)carry);
-        }
-        __syncthreads();
+        // placement of the features in the slice's index buckets
+        place_scan<BPER>(
+            L, tid, R, (int)kCondEntries, [&](uint32_t r) { return L.cnt[r]; },
+            [&](uint32_t r, uint32_t homed_below, uint32_t placed_to) {
+                Te[r] = (uint16_t)homed_below;
+                Tp[r] = (uint16_t)placed_to;
+            });
         const uint32_t placed = Tp[R - 1];
         const uint64_t v0 = c.slice_vals[z];
         uint4* const lines = idx + (uint64_t)z * R * kCondEntries;

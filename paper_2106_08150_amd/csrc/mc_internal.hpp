@@ -27,7 +27,7 @@ enum BuildCounter {
     kCntCand = 2,        // cap candidates pushed (may exceed the list capacity)
     kCntFull = 3,        // inserts that found no free slot
     kCntMoved = 4,       // entries re-inserted by a rehash
-    kCntDefer = 5,       // slice-local inserts whose chain ran past their slice
+    kCntDefer = 5,       // slice-local inserts (or moves) whose chain ran past their slice
     kNumBuildCounters = 8
 };
 
@@ -258,6 +258,15 @@ hipError_t launch_cap_finalize(unsigned long long* table, uint64_t nb, uint32_t 
                                const uint32_t* cand, uint64_t n_cand, hipStream_t st);
 hipError_t launch_cap_scan(unsigned long long* table, uint64_t nb, uint32_t cap,
                            uint32_t cap_dist, hipStream_t st);
+// Table growth, slice by slice: every live entry of the old table into the new
+// one, whose lines and counters are all written (launch_rehash needs them
+// cleared). counters[kCntDefer] above defer_cap: entries were dropped, start
+// over with launch_rehash. Both tables must suit grow_slices_fit.
+bool grow_slices_fit(uint64_t old_nb, uint64_t nb);
+hipError_t launch_grow_slices(const unsigned long long* old_table, uint64_t old_nb,
+                              unsigned long long* table, uint32_t* bcount, uint64_t nb,
+                              unsigned long long* counters, unsigned long long* defer,
+                              uint64_t defer_cap, hipStream_t st);
 hipError_t launch_rehash(const unsigned long long* old_table, uint64_t old_nb,
                          unsigned long long* table, uint32_t* bcount, uint64_t nb,
                          unsigned long long* counters, hipStream_t st);
