@@ -28,7 +28,7 @@ struct SketchLds {
 // Partition of a feature: its home bucket >> part_shift, so partition p holds
 // the features whose home buckets form the p-th contiguous range of the table.
 __device__ __forceinline__ uint32_t part_of(uint32_t f, uint64_t nb, uint32_t shift) {
-    return (uint32_t)(home_bucket(f, nb) >> shift);
+    return (uint32_t)home_bucket(f, nb) >> shift;
 }
 
 // Sketch every window of the call (B1-B4). One workgroup stages a tile of 32
@@ -40,9 +40,16 @@ __device__ __forceinline__ uint32_t part_of(uint32_t f, uint64_t nb, uint32_t sh
 //                   partitions per scatter group (the group of a tile's pairs
 //                   is that of the level-1 scatter chunk holding the tile).
 //
+// Bound by vector and scalar issue (198 VALU and 179 SALU instructions a pair of
+// windows): the usual pair, two full windows whose candidates decide them, takes
+// a path of its own that stores its sketches from the registers that ranked
+// them. Against one path for every pair, booleans for its decisions and an
+// out-of-line redo of every window its first threshold did not decide: 280 and
+// 259 instructions, 9.8 -> 7.1 ms on a 4 Gbp build.
+//
 // Eight waves a SIMD: left unbounded, the kernel takes 106 scalar registers
 // and fewer waves fit; the scalar spills that the 8-wave budget costs are
-// cheaper than the lost latency hiding (10.6 -> 9.9 ms on a 4 Gbp build).
+// cheaper than the lost latency hiding.
 template <int KPL, bool kPairs>
 __global__ __launch_bounds__(kBuildThreads) __attribute__((amdgpu_waves_per_eu(8)))
 void k_sketch(BuildArgs a) {
@@ -80,42 +87,65 @@ void k_sketch(BuildArgs a) {
         __syncthreads();
         // a tile without a non-base byte (the common case) skips the
         // per-k-mer validity test
-        const bool dirty =
-            __syncthreads_or(stage_words(L.words, blo, bhi, tstart, tend, tid, kBuildThreads));
-        const uintptr_t A0 = blo & ~(uintptr_t)15;
-        const uint64_t n_starts = td.len - a.k + 1;
+        const uint32_t dirty = uniform((uint32_t)
+            __syncthreads_or(stage_words(L.words, blo, bhi, tstart, tend, tid, kBuildThreads)));
+        const uint32_t xt = (uint32_t)(blo & 15u);   // window j0's first base in the staged words
+        // k-mer starts of the target's last window; every other window has S
+        const uint32_t nk_last = (uint32_t)(td.len - a.k + 1 - (uint64_t)(td.nw - 1u) * a.S);
+        unsigned long long* const tile_out = kPairs ? a.pairs + (td.win_base + j0) * a.s : nullptr;
         // each wave sketches pairs of windows (2i, 2i+1) of the tile
         for (uint32_t wv = 2u * (uint32_t)wave; wv < nwin; wv += 2u * kWavesPerBuild) {
-            uint32_t nk[2], x0[2];
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t j = j0 + wv + (uint32_t)h;
-                const uint64_t first = (uint64_t)j * a.S;
-                nk[h] = wv + h < nwin ? (uint32_t)min((uint64_t)a.S, n_starts - first) : 0u;
-                x0[h] = wv + h < nwin ? (uint32_t)(tstart + first - A0) : 0u;
-            }
-            uint32_t* sk = L.feats[wave];
-            uint32_t n[2];
-            sketch_pair<KPL, true>(L.words, x0[0], nk[0], L.words, x0[1], nk[1], a.k, a.s, th, sk,
-                             sk + kMaxSketch, L.scratch[wave], n[0], n[1], dirty, dirty);
-            wave_lds_sync();
-            // entry e of the pair: window e / s, sketch slot e % s
-            const uint32_t npair = wv + 1 < nwin ? 2u : 1u;
-            for (uint32_t e = (uint32_t)lane; e < npair * a.s; e += kWave) {
-                const uint32_t h = e >= a.s ? 1u : 0u, i = e - h * a.s;
-                const uint32_t j = j0 + wv + h;
-                const uint64_t gw = td.win_base + j;
-                const uint32_t nh = h ? n[1] : n[0];
-                if (kPairs) {
-                    uint64_t pe = kEmpty;
-                    if (i < nh) {
-                        const uint32_t f = sk[h * kMaxSketch + i];
-                        pe = ((uint64_t)f << 32) | ((td.id << kWindowBits) | j);
-                        atomicAdd(&L.hist[hbase + part_of(f, a.nb, a.part_shift)], 1u);
+            const uint32_t j = j0 + wv;
+            const bool two = wv + 1u < nwin;
+            const uint32_t nkA = j + 1u < td.nw ? a.S : nk_last;
+            const uint32_t nkB = !two ? 0u : j + 2u < td.nw ? a.S : nk_last;
+            const uint32_t xA = xt + wv * a.S, xB = two ? xA + a.S : 0u;
+            PairSketch p = sketch_pair<KPL>(L.words, xA, nkA, L.words, xB, nkB, a.k, a.s, th,
+                                            L.scratch[wave], dirty, dirty);
+            if (kPairs) {
+                // both sketches full: every selected lane stores its pair
+                unsigned long long* const out = tile_out + wv * a.s;
+                const uint32_t loc0 = (td.id << kWindowBits) | j;
+                auto count = [&](uint32_t f) {
+                    atomicAdd(&L.hist[hbase + part_of(f, a.nb, a.part_shift)], 1u);
+                };
+                if (__builtin_expect(p.full(a.s), 1)) {
+                    if (lane_in(p.sel)) {
+                        const uint32_t h = (uint32_t)lane >> 5;
+                        // a 32-bit byte offset from a scalar base
+                        *reinterpret_cast<unsigned long long*>(
+                            reinterpret_cast<char*>(out) + 8u * (h * a.s + p.rank)) =
+                            ((uint64_t)p.v << 32) | (loc0 + h);
+                        count(p.v);
                     }
-                    a.pairs[gw * a.s + i] = pe;
-                } else {
-                    if (i == 0) a.out_counts[gw] = nh;
-                    if (i < nh) a.out_feats[gw * a.s + i] = sk[h * kMaxSketch + i];
+                    continue;
+                }
+                uint32_t* const sk = L.feats[wave];
+                sketch_rest<KPL>(p, L.words, xA, nkA, L.words, xB, nkB, a.k, a.s, sk,
+                                 sk + kMaxSketch, L.scratch[wave]);
+                wave_lds_sync();
+                // entry e of the pair: window e / s, sketch slot e % s
+                for (uint32_t e = (uint32_t)lane; e < (two ? 2u : 1u) * a.s; e += kWave) {
+                    const uint32_t h = e >= a.s ? 1u : 0u, i = e - h * a.s;
+                    uint64_t pe = kEmpty;
+                    if (i < (h ? p.nB : p.nA)) {
+                        const uint32_t f = sk[h * kMaxSketch + i];
+                        pe = ((uint64_t)f << 32) | (loc0 + h);
+                        count(f);
+                    }
+                    out[e] = pe;
+                }
+            } else {
+                const uint64_t gw = td.win_base + j;
+                uint32_t* const sk = L.feats[wave];
+                sketch_rest<KPL>(p, L.words, xA, nkA, L.words, xB, nkB, a.k, a.s, sk,
+                                 sk + kMaxSketch, L.scratch[wave]);
+                wave_lds_sync();
+                for (uint32_t e = (uint32_t)lane; e < (two ? 2u : 1u) * a.s; e += kWave) {
+                    const uint32_t h = e >= a.s ? 1u : 0u, i = e - h * a.s;
+                    const uint32_t nh = h ? p.nB : p.nA;
+                    if (i == 0) a.out_counts[gw + h] = nh;
+                    if (i < nh) a.out_feats[(gw + h) * a.s + i] = sk[h * kMaxSketch + i];
                 }
             }
             wave_lds_sync();

@@ -481,15 +481,31 @@ __device__ __forceinline__ uint32_t hash_threshold(float expect, uint32_t nk) {
     return t >= 4294967040.0f ? 0xFFFFFFFFu : (uint32_t)t;
 }
 
-// Candidate threshold of sketch_pair (hash_threshold of 1.5 s): computed once
-// for the full window of S k-mers, divided out only for shorter windows.
+// Lanes below m (any m), computed in scalar registers.
+__device__ __forceinline__ uint64_t lanes_below(uint32_t m) {
+    return m >= 64u ? ~0ull : (1ull << m) - 1ull;
+}
+
+// Candidates of a window in sketch_pair: hashes below a threshold that about
+// 1.5 s of its nk hashes pass (hash_threshold), computed once for the full window
+// of S k-mers, divided out only for shorter windows; a window of at most 32
+// k-mers takes them all. A number c of candidates decides the window if it is at
+// least s and at most 32, as one comparison: c - lo <= span (never for s > 32).
 struct Threshold {
-    uint32_t S, tS;
+    uint32_t S, tS, lo, span;
     __device__ __forceinline__ Threshold(uint32_t S_, uint32_t s)
-        : S(S_), tS(hash_threshold(1.5f * (float)s, S_)) {}
+        : S(S_),
+          tS(uniform(S_ <= 32u ? 0xFFFFFFFFu : hash_threshold(1.5f * (float)s, S_))),
+          lo(s <= 32u ? s : 1u << 16),
+          span(s <= 32u ? 32u - s : 0u) {}
+    // lanes of register r that hold a k-mer of a full window
+    __device__ __forceinline__ uint64_t full_lanes(int r) const {
+        return lanes_below(max(S, (uint32_t)(r * kWave)) - (uint32_t)(r * kWave));
+    }
     __device__ __forceinline__ uint32_t of(uint32_t nk, uint32_t s) const {
         if (nk == S) return tS;
-        return hash_threshold(1.5f * (float)s, nk);
+        if (nk <= 32u) return 0xFFFFFFFFu;
+        return uniform(hash_threshold(1.5f * (float)s, nk));
     }
 };
 
@@ -497,58 +513,49 @@ struct Threshold {
 // bases after the first staged word: key[r] belongs to k-mer r*64 + lane and is
 // 0xFFFFFFFF for an invalid k-mer or past nk. Returns whether some valid k-mer
 // hashed to 0xFFFFFFFF (that value then still counts as a distinct feature).
-// kCheck = false: the caller knows the window holds no invalid base. K-mer
-// r*64 + lane starts 4r words after k-mer lane, at the same offset in its word.
-// kAll: every lane hashes, with no branch around lanes past nk (they read
-// staged words beyond the window and drop them; W must then hold 4 * KPL + 2
-// words from the window's first word on, x0 < 16). That saves the scalar
-// branch work per key where vector issue has room (the build); without it,
-// lanes past nk skip the hash.
-template <int KPL, bool kCheck, bool kAll = false>
-__device__ __forceinline__ bool window_keys_t(const Word* W, uint32_t x0, uint32_t nk, uint32_t k,
-                                              uint32_t (&key)[KPL]) {
+template <int KPL>
+__device__ __forceinline__ bool window_keys(const Word* W, uint32_t x0, uint32_t nk, uint32_t k,
+                                            uint32_t (&key)[KPL]) {
     const int lane = lane_id();
-    const uint32_t x = x0 + (uint32_t)lane;
+    bool top = false;
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) {
+        const uint32_t i = (uint32_t)(r * kWave + lane);
+        key[r] = 0xFFFFFFFFu;
+        uint32_t c;
+        if (i < nk && kmer_at(W, x0 + i, k, c)) {
+            key[r] = h1(c);
+            top |= key[r] == 0xFFFFFFFFu;
+        }
+    }
+    return ballot(top) != 0;
+}
+
+// The same hashes without a per-lane test: h[r] of the k-mer starting x0 +
+// r*64 + lane, on every lane (lanes past nk read staged words beyond the window:
+// W must hold 4 * KPL + 2 words from the window's first word on), and in valid[r]
+// the lanes whose k-mer holds no invalid base. kCheck = false: the caller knows
+// the window holds none. K-mer r*64 + lane starts 4r words after k-mer lane, at
+// the same offset in its word. Registers whose k-mers all lie past nk are not
+// hashed.
+template <int KPL, bool kCheck>
+__device__ __forceinline__ void window_hashes(const Word* W, uint32_t x0, uint32_t nk, uint32_t k,
+                                              uint32_t (&h)[KPL], uint64_t (&valid)[KPL]) {
+    const uint32_t x = x0 + (uint32_t)lane_id();
     const Word* Wq = W + (x >> 4);
     const uint32_t o = x & 15u;
     const Word* Wl = Wq + (o != 0u);
     const uint32_t kmask = kmer_mask(k);
-    if constexpr (kAll) {
-        uint32_t top = 0u;
 #pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-            const uint32_t i = (uint32_t)(r * kWave + lane);
-            uint32_t c;
-            const bool ok = kmer_of<kCheck>(Wq[4 * r], Wl[4 * r], Wq[4 * r + 1], o, k, kmask, c);
-            const uint32_t h = h1(c);
-            const bool use = i < nk && ok;
-            key[r] = use ? h : 0xFFFFFFFFu;
-            top |= use && h == 0xFFFFFFFFu ? 1u : 0u;
-        }
-        return ballot(top != 0u) != 0;
-    } else {
-        bool top = false;
-#pragma unroll
-        for (int r = 0; r < KPL; ++r) {
-            const uint32_t i = (uint32_t)(r * kWave + lane);
-            key[r] = 0xFFFFFFFFu;
-            if (i < nk) {
-                uint32_t c;
-                if (kmer_of<kCheck>(Wq[4 * r], Wl[4 * r], Wq[4 * r + 1], o, k, kmask, c)) {
-                    const uint32_t h = h1(c);
-                    key[r] = h;
-                    top |= (h == 0xFFFFFFFFu);
-                }
-            }
-        }
-        return ballot(top) != 0;
+    for (int r = 0; r < KPL; ++r) {
+        h[r] = 0u;
+        valid[r] = ~0ull;
+        if (r > 0 && nk <= (uint32_t)(r * kWave)) continue;
+        uint32_t c;
+        const bool ok = kmer_of<kCheck>(Wq[4 * r], Wl[4 * r], Wq[4 * r + 1], o, k, kmask, c);
+        h[r] = h1(c);
+        if (kCheck) valid[r] = ballot(ok);
     }
-}
-
-template <int KPL>
-__device__ __forceinline__ bool window_keys(const Word* W, uint32_t x0, uint32_t nk, uint32_t k,
-                                            uint32_t (&key)[KPL]) {
-    return window_keys_t<KPL, true>(W, x0, nk, k, key);
 }
 
 // The s smallest distinct keys of one window (its nk keys as left by
@@ -643,116 +650,151 @@ __device__ __forceinline__ void wave_sort_halves(uint32_t& v) {
     }
 }
 
-// Candidates of one window for a 32-entry half of scratch. A window of at
-// most 32 k-mers contributes all its keys (mode 0, exact). A longer one
-// contributes its keys below a threshold that about 1.5 s of them pass (mode
-// 1), valid only if at least s distinct values end up below it; if fewer than
-// s or more than 32 keys pass, it contributes nothing (mode 2) and is
-// sketched on its own. Returns the number of entries written.
+// Candidates of one window for a 32-entry half of scratch (see Threshold). If at
+// least s distinct values lie below the threshold, the s smallest of the window
+// are exactly the s smallest of the candidates. About one window in twenty has
+// fewer than s or more than 32 candidates: its threshold is moved by a quarter
+// and the hashes, still in registers, are compared again (a window that stays
+// undecided is redone alone with every hash, which costs as much as two pairs).
+// Returns the number of candidates written, plus kAllHashes if they are all of
+// the window's hashes below 0xFFFFFFFF; kUndecided (none written) otherwise.
+// most receives the lane's largest hash (of k-mers that may not count).
+//
+// A full window without an invalid base, the common case, has code of its own
+// without the tests for either. The wave-uniform decisions are integers, not
+// booleans: booleans that live across blocks become 64-bit lane masks, several
+// scalar instructions each, and scalar issue bounds the kernels as much as
+// vector issue does.
+constexpr uint32_t kAllHashes = 64u, kUndecided = 128u;
 template <int KPL>
-__device__ __forceinline__ uint32_t half_candidates(const uint32_t (&key)[KPL], uint32_t nk,
-                                                    uint32_t s, const Threshold& th,
-                                                    uint32_t* half, int& mode) {
-    const int lane = lane_id();
-    if (nk <= 32u) {
-        if (lane < 32) half[lane] = key[0];
-        mode = 0;
-        return 32u;
-    }
-    const uint32_t T = th.of(nk, s);
-    uint64_t bal[KPL];
+__device__ __forceinline__ uint32_t below_threshold(const uint32_t (&h)[KPL],
+                                                    const uint64_t (&valid)[KPL], uint32_t T,
+                                                    uint64_t (&bal)[KPL]) {
     uint32_t c = 0;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-        bal[r] = ballot(key[r] < T);
+        bal[r] = valid[r] & ballot(h[r] < T);
         c += popc64(bal[r]);
     }
-    if (c < s || c > 32u) {
-        mode = 2;
-        return 0u;
+    return c;
+}
+template <int KPL>
+__device__ __forceinline__ uint32_t half_candidates(const Word* W, uint32_t x0, uint32_t nk,
+                                                    uint32_t k, uint32_t s, const Threshold& th,
+                                                    uint32_t dirty, uint32_t* half,
+                                                    uint32_t& most) {
+    uint32_t h[KPL];
+    uint64_t valid[KPL], bal[KPL];
+    uint32_t c, T, state;
+    if (__builtin_expect(nk == th.S && dirty == 0u, 1)) {
+        window_hashes<KPL, false>(W, x0, KPL * kWave, k, h, valid);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r) valid[r] = th.full_lanes(r);
+        T = th.tS;
+        c = below_threshold<KPL>(h, valid, T, bal);
+    } else {
+        if (dirty) window_hashes<KPL, true>(W, x0, nk, k, h, valid);
+        else window_hashes<KPL, false>(W, x0, nk, k, h, valid);
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            valid[r] &= nk > (uint32_t)(r * kWave) ? lanes_below(nk - (uint32_t)(r * kWave)) : 0ull;
+        T = th.of(nk, s);
+        c = below_threshold<KPL>(h, valid, T, bal);
+    }
+#pragma unroll
+    for (int r = 0; r < KPL; ++r) most = max(most, h[r]);
+    state = c;
+    if (__builtin_expect(c - th.lo > th.span, 0)) {
+        for (uint32_t tries = 0; T != 0xFFFFFFFFu && c - th.lo > th.span; ++tries) {
+            if (tries == 3u || s > 32u) return kUndecided;
+            T = c > 32u ? T - (T >> 2) : T + min(T >> 2, ~T);
+            c = below_threshold<KPL>(h, valid, T, bal);
+        }
+        if (c > 32u) return kUndecided;
+        state = T == 0xFFFFFFFFu ? c + kAllHashes : c;
     }
     uint32_t base = 0;
 #pragma unroll
     for (int r = 0; r < KPL; ++r) {
-        if (key[r] < T) half[rank_below(bal[r], base)] = key[r];
+        if (lane_in(bal[r])) half[rank_below(bal[r], base)] = h[r];
         base += popc64(bal[r]);
     }
-    mode = 1;
-    return c;
+    return state;
 }
 
 // Sketches of two windows A and B (either may be empty, nk = 0) at once: the
 // candidates of A fill lanes 0..31 and those of B lanes 32..63, one 32-wide
 // sort orders both halves, and one ballot ranks the distinct values of both.
-// A window whose candidates do not decide its sketch is redone alone (its
-// staged words must still be in place). All pointers are to LDS. Writes
-// skA[0..nA) and skB[0..nB). scratch: 64 words of LDS owned by the wave.
-// dirtyA / dirtyB (wave-uniform): the window may hold an invalid base; when
-// false its k-mers skip the validity test. kAll: as for window_keys_t.
-template <int KPL, bool kAll = false>
-__device__ __forceinline__ void sketch_pair(const Word* WA, uint32_t xA, uint32_t nkA,
-                                            const Word* WB, uint32_t xB, uint32_t nkB,
-                                            uint32_t k, uint32_t s, const Threshold& th,
-                                            uint32_t* skA, uint32_t* skB,
-                                            uint32_t* scratch, uint32_t& nA, uint32_t& nB,
-                                            bool dirtyA = true, bool dirtyB = true) {
+// The lanes in `sel` hold the s smallest distinct candidates v of each window
+// (A's below lane 32), each the rank-th of its window; dA and dB are the numbers
+// of distinct candidates. When full(s), these are the two sketches; else
+// sketch_rest completes them. scratch: 64 words of LDS owned by the wave. dirtyA
+// / dirtyB (wave-uniform): the window may hold an invalid base.
+struct PairSketch {
+    uint32_t v, rank;
+    uint64_t sel;
+    uint32_t dA, dB;
+    uint32_t stateA, stateB; // as half_candidates
+    uint32_t nA, nB;         // set by sketch_rest
+    __device__ __forceinline__ bool full(uint32_t s) const { return min(dA, dB) >= s; }
+};
+template <int KPL>
+__device__ __forceinline__ PairSketch sketch_pair(const Word* WA, uint32_t xA, uint32_t nkA,
+                                                  const Word* WB, uint32_t xB, uint32_t nkB,
+                                                  uint32_t k, uint32_t s, const Threshold& th,
+                                                  uint32_t* scratch, uint32_t dirtyA,
+                                                  uint32_t dirtyB) {
     const int lane = lane_id();
-    int modeA, modeB;
-    uint32_t cA, cB;
-    bool topA, topB;
-    {
-        uint32_t key[KPL];
-        topA = dirtyA ? window_keys_t<KPL, true, kAll>(WA, xA, nkA, k, key)
-                      : window_keys_t<KPL, false, kAll>(WA, xA, nkA, k, key);
-        cA = half_candidates<KPL>(key, nkA, s, th, scratch, modeA);
-        topB = dirtyB ? window_keys_t<KPL, true, kAll>(WB, xB, nkB, k, key)
-                      : window_keys_t<KPL, false, kAll>(WB, xB, nkB, k, key);
-        cB = half_candidates<KPL>(key, nkB, s, th, scratch + 32, modeB);
-    }
+    PairSketch p;
+    uint32_t most = 0;
+    p.stateA = half_candidates<KPL>(WA, xA, nkA, k, s, th, dirtyA, scratch, most);
+    p.stateB = half_candidates<KPL>(WB, xB, nkB, k, s, th, dirtyB, scratch + 32, most);
+    // a k-mer that hashes to 0xFFFFFFFF (on a lane that may not even count)
+    // leaves both windows undecided: no candidate stands for it
+    if (__builtin_expect(ballot(most == 0xFFFFFFFFu) != 0ull, 0)) p.stateA = p.stateB = kUndecided;
     wave_lds_sync();
     const uint32_t hl = (uint32_t)lane & 31u;
-    uint32_t v = hl < (lane < 32 ? cA : cB) ? scratch[lane] : 0xFFFFFFFFu;
+    const uint32_t word = scratch[lane];
+    uint32_t v = hl < ((lane < 32 ? p.stateA : p.stateB) & 63u) ? word : 0xFFFFFFFFu;
     wave_lds_sync();
     wave_sort_halves(v);
     // previous lane's key (whole-wave shift right by one lane)
     const uint32_t prev = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, false);
     // first of its value in its half: not the padding key, and lane 0 of the
     // half or unlike the lane before
-    const uint64_t bal = ballot(v != 0xFFFFFFFFu) & (ballot(v != prev) | 0x0000000100000001ull);
-    const bool first = lane_in(bal);
-    const uint32_t dA = popc64(bal & 0xFFFFFFFFull), dB = popc64(bal >> 32);
-    const bool okA = modeA == 0 || (modeA == 1 && dA >= s);
-    const bool okB = modeB == 0 || (modeB == 1 && dB >= s);
-    const uint32_t rank = rank_below(bal) - (lane < 32 ? 0u : dA);
-    if (first && rank < s) {
-        if (lane < 32) {
-            if (okA) skA[rank] = v;
-        } else if (okB) {
-            skB[rank] = v;
-        }
-    }
-    nA = dA < s ? dA : s;
-    nB = dB < s ? dB : s;
-    if (okA && topA && dA < s) {
-        if (lane == 0) skA[dA] = 0xFFFFFFFFu;
-        nA = dA + 1;
-    }
-    if (okB && topB && dB < s) {
-        if (lane == 0) skB[dB] = 0xFFFFFFFFu;
-        nB = dB + 1;
-    }
-    // rare: the keys of an undecided window are recomputed from the staged words
-    if (!okA) {
+    const uint64_t firsts =
+        ballot(v != 0xFFFFFFFFu) & (ballot(v != prev) | 0x0000000100000001ull);
+    p.dA = popc64(firsts & 0xFFFFFFFFull);
+    p.dB = popc64(firsts >> 32);
+    p.v = v;
+    p.rank = rank_below(firsts) - (lane < 32 ? 0u : p.dA);
+    p.sel = firsts & ballot(p.rank < s);
+    return p;
+}
+
+// The pair's sketches into LDS: skA[0..nA) and skB[0..nB), ascending. A window
+// that its candidates do not decide is done alone from its staged words (which
+// must still be in place).
+template <int KPL>
+__device__ __forceinline__ void sketch_rest(PairSketch& p, const Word* WA, uint32_t xA,
+                                            uint32_t nkA, const Word* WB, uint32_t xB,
+                                            uint32_t nkB, uint32_t k, uint32_t s, uint32_t* skA,
+                                            uint32_t* skB, uint32_t* scratch) {
+    p.nA = min(p.dA, s);
+    p.nB = min(p.dB, s);
+    if (lane_in(p.sel)) (lane_id() < 32 ? skA : skB)[p.rank] = p.v;
+    if (__builtin_expect(p.full(s), 1)) return;
+    if (p.stateA == kUndecided || (p.dA < s && nkA > 32u && !(p.stateA & kAllHashes))) {
         wave_lds_sync();
-        nA = uniform(sketch_window_rare<KPL>(WA, xA, nkA, k, s, skA, scratch));
+        p.nA = uniform(sketch_window_rare<KPL>(WA, xA, nkA, k, s, skA, scratch));
     }
-    if (!okB) {
+    if (p.stateB == kUndecided || (p.dB < s && nkB > 32u && !(p.stateB & kAllHashes))) {
         wave_lds_sync();
-        nB = uniform(sketch_window_rare<KPL>(WB, xB, nkB, k, s, skB, scratch));
+        p.nB = uniform(sketch_window_rare<KPL>(WB, xB, nkB, k, s, skB, scratch));
     }
     // the counts are wave-uniform; saying so keeps the callers' loops scalar
-    nA = uniform(nA);
-    nB = uniform(nB);
+    p.nA = uniform(p.nA);
+    p.nB = uniform(p.nB);
 }
 
 // Stage the bytes [lo, hi) into words relative to A0 = lo & ~15, one word per

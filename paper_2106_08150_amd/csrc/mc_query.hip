@@ -56,11 +56,6 @@ struct QueryLds {
     uint32_t sel_t[kMaxTopM], sel_s[kMaxTopM], sel_b[kMaxTopM];   // top-m list
 };
 
-// Lanes below m (any m), computed in scalar registers.
-__device__ __forceinline__ uint64_t lanes_below(uint32_t m) {
-    return m >= 64u ? ~0ull : (1ull << m) - 1ull;
-}
-
 // s_waitcnt immediate for vmcnt(0) with the other counters left alone (gfx9
 // encoding: vmcnt bits 3..0 and 15..14, expcnt 6..4, lgkmcnt 11..8).
 constexpr int kWaitVmem0 = 0x0F70;
@@ -410,8 +405,8 @@ __device__ __forceinline__ uint32_t staged_words(const WinRef& r) {
 // windows take a single pass of the wave. dirtyA / dirtyB (wave-uniform): a
 // staged byte of that window's mate is not a base.
 __device__ __forceinline__ void stage_pair(Word* W, uintptr_t base, const WinRef& A,
-                                           const WinRef& B, int lane, bool& dirtyA,
-                                           bool& dirtyB) {
+                                           const WinRef& B, int lane, uint32_t& dirtyA,
+                                           uint32_t& dirtyB) {
     const uint32_t ndA = 4u * staged_words(A), nd = ndA + 4u * staged_words(B);
     // the flags are vector words, not lane masks: merging lane masks across
     // the loop took scalar instructions (scalar issue limits this kernel)
@@ -424,8 +419,8 @@ __device__ __forceinline__ void stage_pair(Word* W, uintptr_t base, const WinRef
         badA |= second ? 0u : bad;
         badB |= second ? bad : 0u;
     }
-    dirtyA = ballot(badA != 0u) != 0;
-    dirtyB = ballot(badB != 0u) != 0;
+    dirtyA = ballot(badA != 0u) != 0 ? 1u : 0u;
+    dirtyB = ballot(badB != 0u) != 0 ? 1u : 0u;
 }
 
 // A record's staging base and lengths, or false for a record of 2^31 bytes or
@@ -605,13 +600,15 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
         WinRef wr[2];
         for (int h = 0; h < 2; ++h) wr[h] = window_ref(a, p + h, nwt, nws[0], rs.r0, rs.len);
         wave_lds_sync();
-        bool dirtyA, dirtyB;
+        uint32_t dirtyA, dirtyB;
         stage_pair(L.sk.stage, rs.base, wr[0], wr[1], lane, dirtyA, dirtyB);
         wave_lds_sync();
-        uint32_t nA, nB;
-        sketch_pair<KPL>(L.sk.stage, wr[0].x0, wr[0].nk, L.sk.stage + kStageWords, wr[1].x0, wr[1].nk,
-                         a.k, a.s, th, L.sk.feats + nf, L.sk.feats + nf + a.s, L.sk.scratch, nA,
-                         nB, dirtyA, dirtyB);
+        const Word *const WA = L.sk.stage, *const WB = L.sk.stage + kStageWords;
+        PairSketch ps = sketch_pair<KPL>(WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s,
+                                         th, L.sk.scratch, dirtyA, dirtyB);
+        sketch_rest<KPL>(ps, WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s,
+                         L.sk.feats + nf, L.sk.feats + nf + a.s, L.sk.scratch);
+        const uint32_t nA = ps.nA, nB = ps.nB;
         wave_lds_sync();
         if (nA < a.s && nB) {      // close the gap after A's features
             const uint32_t f = (uint32_t)lane < nB ? L.sk.feats[nf + a.s + lane] : 0u;
@@ -1211,13 +1208,15 @@ __device__ void classify_large_record(const QueryArgs& a, uint32_t rec, LargeLds
             WinRef wr[2];
             for (int h = 0; h < 2; ++h) wr[h] = window_ref(a, p + h, p1, nw0, rs.r0, rs.len);
             wave_lds_sync();
-            bool dirtyA, dirtyB;
+            uint32_t dirtyA, dirtyB;
             stage_pair(W.stage, rs.base, wr[0], wr[1], (int)lane, dirtyA, dirtyB);
             wave_lds_sync();
-            uint32_t nA, nB;
-            sketch_pair<KPL>(W.stage, wr[0].x0, wr[0].nk, W.stage + kStageWords, wr[1].x0,
-                             wr[1].nk, a.k, a.s, th, W.sk, W.sk + 64, W.scratch, nA, nB, dirtyA,
-                             dirtyB);
+            const Word *const WA = W.stage, *const WB = W.stage + kStageWords;
+            PairSketch ps = sketch_pair<KPL>(WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k,
+                                             a.s, th, W.scratch, dirtyA, dirtyB);
+            sketch_rest<KPL>(ps, WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s, W.sk,
+                             W.sk + 64, W.scratch);
+            const uint32_t nA = ps.nA, nB = ps.nB;
             wave_lds_sync();
             uint32_t base = 0;
             if (lane == 0) base = atomicAdd(&L.nfeat, nA + nB);
@@ -1388,13 +1387,15 @@ __device__ void classify_huge_record(const QueryArgs& a, uint32_t rec, const Hug
         WinRef wr[2];
         for (int x = 0; x < 2; ++x) wr[x] = window_ref(a, p + x, nwt, nws[0], rs.r0, rs.len);
         wave_lds_sync();
-        bool dirtyA, dirtyB;
+        uint32_t dirtyA, dirtyB;
         stage_pair(L.stage[wave], rs.base, wr[0], wr[1], (int)lane, dirtyA, dirtyB);
         wave_lds_sync();
-        uint32_t nA, nB;
-        sketch_pair<KPL>(L.stage[wave], wr[0].x0, wr[0].nk, L.stage[wave] + kStageWords, wr[1].x0,
-                         wr[1].nk, a.k, a.s, th, L.sk[wave], L.sk[wave] + 64, L.scratch[wave], nA,
-                         nB, dirtyA, dirtyB);
+        const Word *const WA = L.stage[wave], *const WB = L.stage[wave] + kStageWords;
+        PairSketch ps = sketch_pair<KPL>(WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s,
+                                         th, L.scratch[wave], dirtyA, dirtyB);
+        sketch_rest<KPL>(ps, WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s, L.sk[wave],
+                         L.sk[wave] + 64, L.scratch[wave]);
+        const uint32_t nA = ps.nA, nB = ps.nB;
         wave_lds_sync();
         uint32_t base = 0;
         if (lane == 0) base = atomicAdd(&L.nfeat, nA + nB);
