@@ -64,6 +64,114 @@ constexpr int kWaitVmem0 = 0x0F70;
 // 8-lane group reads.
 constexpr uint64_t kLastSlots = 0x8080808080808080ull;
 
+// Inclusive prefix sum over the lanes.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    return v;
+}
+
+// Queue the next bucket of the items whose lane is set in `full`: lane
+// 8g + 4 + q stands for item 8q + g of the batch, which it reads again from the
+// ring. One pass for the batch; a pass per step took as many instructions for
+// each one's one or two items.
+__device__ __forceinline__ void requeue(const QueryArgs& a, uint64_t full, const uint2* batch,
+                                        uint32_t l3, uint2* ring, uint32_t& tail) {
+    uint2 it = batch[8u * l3];                // batch: the lane's group's item of step 0
+    // the bucket count is read here, not held across the loop
+    it.y = it.y + 1u == (uint32_t)MC_COLD(nb) ? 0u : it.y + 1u;
+    const uint32_t pos = rank_below(full, tail) & (kRing - 1u);
+    wave_lds_sync();                          // a full ring's new items replace the batch's
+    if (lane_in(full)) {
+        ring[pos] = it;
+        if (pos < kRingMirror) ring[pos + kRing] = it;
+    }
+    tail += popc64(full);
+}
+
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+constexpr uint32_t kGroups = 8;      // groups of 8 lanes, one bucket line each
+constexpr int kBatchSteps = 4;       // lines in flight a group
+
+// The work items of features F[0..nf) at their home buckets.
+__device__ __forceinline__ void fill_ring(const QueryArgs& a, const uint32_t* F, uint32_t nf,
+                                          uint2* ring) {
+    for (uint32_t i = (uint32_t)lane_id(); i < nf; i += kWave) {
+        const uint2 it = make_uint2(F[i], (uint32_t)home_bucket(F[i], a.nb));
+        ring[i] = it;
+        if (i < kRingMirror) ring[i + kRing] = it;
+    }
+    wave_lds_sync();
+}
+
+// One batch of lookup: c <= 8 NB items (kWhole: exactly that many), l3 the
+// lane's place in its quad. Returns false if its hits do not fit the list.
+template <uint32_t LCAP, int NB, bool kWhole>
+__device__ __forceinline__ bool lookup_batch(const QueryArgs& a, const u64x2* slot2,
+                                             const uint2* batch, uint32_t c, uint32_t l3,
+                                             uint2* ring, uint32_t* list, uint32_t& nlist,
+                                             uint32_t& tail) {
+    const uint32_t lane = (uint32_t)lane_id();
+    const uint32_t g = lane >> 3;
+    uint32_t f[NB], b[NB];
+    u64x2 sl[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        const uint2 it = batch[kGroups * q];
+        f[q] = it.x;
+        b[q] = it.y;
+    }
+    // groups past the batch's last item load nothing and hold empty slots
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        if (!kWhole) sl[q].x = sl[q].y = ~0ull;
+        if (kWhole || (int)g < (int)(c - kGroups * q)) sl[q] = slot2[(uint64_t)b[q] * (kSlots / 2)];
+    }
+    // A slot is the item's if it holds the item's feature and a stored
+    // location (not a tombstone): one 64-bit compare of the slot with the
+    // feature taken off. The kernel is bound by instruction issue, scalar as
+    // much as vector, so hits are counted a lane and placed by one prefix sum
+    // a batch; a wave's hit masks in scalar registers took 15 scalar
+    // instructions a slot and step more. With the requeue once a batch and the
+    // shorter record header, 10M reads of 150 bases on 1 Gbp: 757 -> 619
+    // scalar instructions a read, 14.84 -> 13.5 ms (385M random lines alone
+    // would take 10 ms).
+    uint32_t nh = 0, fl = 0;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        const uint64_t fq = (uint64_t)f[q] << 32;
+        sl[q].x ^= fq;
+        sl[q].y ^= fq;
+        nh += sl[q].x < kTombLoc ? 1u : 0u;
+        nh += sl[q].y < kTombLoc ? 1u : 0u;
+        // full: the location word of the last slot is not all ones (empty)
+        fl |= (uint32_t)sl[q].y != 0xFFFFFFFFu ? 1u << q : 0u;
+    }
+    asm volatile("" : "+v"(fl));
+    const uint32_t incl = wave_prefix(nh);
+    const uint32_t total = nlist + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    if (total > LCAP) return false;
+    uint32_t* out = list + nlist + incl;
+    nlist = total;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        // compared again: the masks would take 16 scalar registers
+        asm volatile("" : "+v"(sl[q]));
+        if (sl[q].x < kTombLoc) *--out = (uint32_t)sl[q].x;
+        if (sl[q].y < kTombLoc) *--out = (uint32_t)sl[q].y;
+    }
+    // lane 8g + 4 + q: whether group g's bucket of step q is full
+    // (quad broadcast of lane 3, to the odd quads)
+    const uint32_t gf = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)fl, 0xFF, 0xF, 0xA, false);
+    const uint64_t full = ballot(((gf >> l3) & 1u) != 0u);
+    if (full) requeue(a, full, batch, l3, ring, tail);
+    return true;
+}
+
 // Append the locations of features F[0..nf) to list (LDS). A work item is a
 // (feature, bucket) pair; the wave takes up to 8 * NB items at a time, item
 // 8q + g read by 8-lane group g as one 128-byte bucket line (16 bytes, two
@@ -75,89 +183,40 @@ constexpr uint64_t kLastSlots = 0x8080808080808080ull;
 // every ring entry always holds some item of the launch (the ring is cleared
 // to bucket 0 when a wave starts), so groups past a batch's last item may read
 // any entry and their lines are simply ignored. Returns false once the list
-// outgrew LCAP (locations past LCAP + 64 are then not stored: the record goes
-// to the large-list pass). junk holds one word per lane that lanes without a
-// hit store into.
+// would outgrow LCAP (the record goes to the large-list pass).
 template <uint32_t LCAP>
 __device__ bool lookup(const QueryArgs& a, const uint32_t* F, uint32_t nf, uint2* ring,
-                       uint32_t* list, uint32_t* junk, uint32_t& nlist, uint32_t& probes) {
-    constexpr int NB = 4;
-    constexpr uint32_t G = 8;            // groups of 8 lanes, one bucket line each
+                       uint32_t* list, uint32_t& nlist, uint32_t& probes) {
     const uint32_t lane = (uint32_t)lane_id();
-    const uint32_t g = lane >> 3;
-    for (uint32_t i = lane; i < nf; i += kWave) {
-        const uint2 it = make_uint2(F[i], (uint32_t)home_bucket(F[i], a.nb));
-        ring[i] = it;
-        if (i < kRingMirror) ring[i + kRing] = it;
-    }
-    wave_lds_sync();
+    fill_ring(a, F, nf, ring);
     // slots 2 (lane & 7) and 2 (lane & 7) + 1 of a bucket, as one 16-byte load
-    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
-    const u64x2* slot2 = reinterpret_cast<const u64x2*>(a.table) + (lane & 7u);
+    const u64x2* const slot2 = reinterpret_cast<const u64x2*>(a.table) + (lane & 7u);
+    uint32_t l3 = lane & 3u;
+    asm volatile("" : "+v"(l3));
     uint32_t head = 0, tail = nf;
     while (head < tail) {
         // every line issued so far has been used; saying so here lets this
         // batch's loads go out back to back (the compiler cannot tell which
         // of the previous batch's loads were issued)
         __builtin_amdgcn_s_waitcnt(kWaitVmem0);
-        const uint32_t c = min(tail - head, G * NB);
-        uint32_t f[NB], b[NB];
-        u64x2 sl[NB];
-        const uint2* batch = ring + ((head & (kRing - 1u)) + g);   // item 8q + g at batch[8q]
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const uint2 it = batch[G * q];
-            f[q] = it.x;
-            b[q] = it.y;
-        }
-        // groups past the batch's last item load nothing (their lines would
-        // be fetched only to be ignored); the mask of the groups holding an
-        // item keeps their unloaded values out of every result
-#pragma unroll
-        for (int q = 0; q < NB; ++q)
-            if (G * q + g < c) sl[q] = slot2[(uint64_t)b[q] * (kSlots / 2)];
+        const uint32_t c = min(tail - head, kGroups * kBatchSteps);
+        // item 8q + g at batch[8q]
+        const uint2* const batch = ring + ((head & (kRing - 1u)) + (lane >> 3));
         head += c;
         probes += c;
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            if (G * q >= c) break;
-            const uint32_t nv = min(c - G * q, G);   // groups holding an item
-            // lanes of the groups holding an item: one vector compare (scalar
-            // issue, not vector issue, limits this kernel)
-            const uint64_t held = ballot(g < nv);
-            const unsigned long long s0 = sl[q].x, s1 = sl[q].y;
-            // a slot is the item's if it holds the item's feature and a
-            // stored location (not a tombstone); the last slot of a bucket is
-            // occupied unless its location word is all ones (empty)
-            const uint64_t hit0 = held & ballot((uint32_t)(s0 >> 32) == f[q]) &
-                                  ballot((uint32_t)s0 < kTombLoc);
-            const uint64_t hit1 = held & ballot((uint32_t)(s1 >> 32) == f[q]) &
-                                  ballot((uint32_t)s1 < kTombLoc);
-            if (hit0 | hit1) {
-                // every lane stores both slots, those without a hit into a
-                // word of their own (no branch around the stores); nlist <=
-                // LCAP here, so hit0's entries stay below LCAP + 64
-                const uint32_t n0 = popc64(hit0);
-                const uint32_t i1 = rank_below(hit1, nlist + n0);
-                uint32_t* const d0 = lane_in(hit0) ? list + rank_below(hit0, nlist) : junk + lane;
-                uint32_t* const d1 = lane_in(hit1) && i1 < LCAP + kWave ? list + i1 : junk + lane;
-                *d0 = (uint32_t)s0;
-                *d1 = (uint32_t)s1;
-                nlist += n0 + popc64(hit1);
-                if (nlist > LCAP) return false;
-            }
-            const uint64_t full = held & kLastSlots & ballot((uint32_t)s1 != 0xFFFFFFFFu);
-            if (full) {
-                if (lane_in(full)) {
-                    // the bucket count is read here, not held across the loop
-                    const uint32_t nxt = b[q] + 1u == (uint32_t)MC_COLD(nb) ? 0u : b[q] + 1u;
-                    const uint32_t pos = (tail + rank_below(full)) & (kRing - 1u);
-                    ring[pos] = make_uint2(f[q], nxt);
-                    if (pos < kRingMirror) ring[pos + kRing] = make_uint2(f[q], nxt);
-                }
-                tail += popc64(full);
-            }
-        }
+        // a whole batch (two full windows of a read) needs no masks; a batch
+        // of at most a line a group (mostly second buckets of chains) takes
+        // one step: 14.0 -> 13.5 ms for 10M reads of 150 bases on 1 Gbp
+        bool fits;
+        if (c == kGroups * kBatchSteps)
+            fits = lookup_batch<LCAP, kBatchSteps, true>(a, slot2, batch, c, l3, ring, list, nlist,
+                                                         tail);
+        else if (c > kGroups)
+            fits = lookup_batch<LCAP, kBatchSteps, false>(a, slot2, batch, c, l3, ring, list,
+                                                          nlist, tail);
+        else
+            fits = lookup_batch<LCAP, 1, false>(a, slot2, batch, c, l3, ring, list, nlist, tail);
+        if (!fits) return false;
         wave_lds_sync();
     }
     return true;
@@ -174,51 +233,61 @@ __device__ bool lookup(const QueryArgs& a, const uint32_t* F, uint32_t nf, uint2
 template <uint32_t LCAP>
 __device__ bool lookup_cond(const QueryArgs& a, const uint32_t* F, uint32_t nf, uint2* ring,
                             uint32_t* list, uint32_t* runs, uint32_t& nlist, uint32_t& probes) {
-    constexpr int NB = 4;
-    constexpr uint32_t G = 8;
+    constexpr int NB = kBatchSteps;
     const uint32_t lane = (uint32_t)lane_id();
     const uint32_t g = lane >> 3;
-    for (uint32_t i = lane; i < nf; i += kWave) {
-        const uint2 it = make_uint2(F[i], (uint32_t)home_bucket(F[i], a.nb));
-        ring[i] = it;
-        if (i < kRingMirror) ring[i + kRing] = it;
-    }
-    wave_lds_sync();
+    fill_ring(a, F, nf, ring);
     const uint4* ent = reinterpret_cast<const uint4*>(a.table) + (lane & 7u);
+    uint32_t l3 = lane & 3u;
+    asm volatile("" : "+v"(l3));
     uint32_t head = 0, tail = nf;
     while (head < tail) {
         __builtin_amdgcn_s_waitcnt(kWaitVmem0);
-        const uint32_t c = min(tail - head, G * NB);
+        const uint32_t c = min(tail - head, kGroups * NB);
+        const uint2* const batch = ring + ((head & (kRing - 1u)) + g);
         uint32_t f[NB], b[NB];
         uint4 e[NB];
-        const uint2* batch = ring + ((head & (kRing - 1u)) + g);
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
-            const uint2 it = batch[G * q];
+            const uint2 it = batch[kGroups * q];
             f[q] = it.x;
             b[q] = it.y;
         }
 #pragma unroll
-        for (int q = 0; q < NB; ++q)   // idle groups load nothing (see lookup)
-            if (G * q + g < c) e[q] = ent[(uint64_t)b[q] * kCondEntries];
+        for (int q = 0; q < NB; ++q) {   // idle groups load nothing and hold empty entries
+            e[q].y = 0u;
+            if ((int)g < (int)(c - kGroups * q)) e[q] = ent[(uint64_t)b[q] * kCondEntries];
+        }
         head += c;
-        uint32_t nrun = 0;   // runs of this batch (at most one a group and q: 32)
+        probes += c;
+        // found and full, one bit a step, and inline locations, a lane at a
+        // time (see lookup_batch); an entry that is not the item's counts 0
+        uint32_t nh = 0, fl = 0, found = 0;
+        uint64_t any_run = 0;
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
-            if (G * q >= c) break;
-            const uint32_t nv = min(c - G * q, G);
-            probes += nv;
-            const uint64_t used = ballot(g < nv) & ballot(e[q].y != 0u);   // occupied entries
-            const uint64_t mine = used & ballot(e[q].x == f[q]);
-            const uint64_t small = ballot(e[q].y <= kCondInline);
-            const uint64_t hitA = mine & small, hitR = mine & ~small;
-            const uint64_t hitB = hitA & ballot(e[q].y == 2u);
-            if (hitA | hitR) {
-                const uint32_t nA = popc64(hitA);
-                if (nlist + nA + popc64(hitB) > LCAP) return false;
-                if (lane_in(hitA)) list[rank_below(hitA, nlist)] = e[q].z;
-                if (lane_in(hitB)) list[rank_below(hitB, nlist + nA)] = e[q].w;
-                nlist += nA + popc64(hitB);
+            fl |= e[q].y != 0u ? 1u << q : 0u;
+            if (e[q].x != f[q]) e[q].y = 0u;
+            found |= e[q].y != 0u ? 1u << q : 0u;
+            nh += e[q].y <= kCondInline ? e[q].y : 0u;
+            any_run |= ballot(e[q].y > kCondInline);
+        }
+        asm volatile("" : "+v"(fl), "+v"(found));
+        const uint32_t incl = wave_prefix(nh);
+        const uint32_t total = nlist + (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (total > LCAP) return false;
+        uint32_t* out = list + nlist + incl;
+        nlist = total;
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            if (e[q].y - 1u < kCondInline) *--out = e[q].z;
+            if (e[q].y == 2u) *--out = e[q].w;
+        }
+        uint32_t nrun = 0;   // runs of this batch (at most one a group and q: 32)
+        if (any_run) {
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const uint64_t hitR = ballot(e[q].y > kCondInline);
                 if (lane_in(hitR)) {
                     const uint32_t r = nrun + rank_below(hitR);
                     runs[3 * r + 0] = e[q].y;
@@ -227,25 +296,17 @@ __device__ bool lookup_cond(const QueryArgs& a, const uint32_t* F, uint32_t nf, 
                 }
                 nrun += popc64(hitR);
             }
-            // a group that did not find its feature in a full line goes on:
-            // spread each group's found bits to its lowest lane, move that to
-            // its last lane, and keep the full lines' last lanes without one
-            uint64_t gf = mine;
-            gf |= gf >> 1;
-            gf |= gf >> 2;
-            gf |= gf >> 4;
-            const uint64_t full = used & kLastSlots & ~((gf & 0x0101010101010101ull) << 7);
-            if (full) {
-                if (lane_in(full)) {
-                    // the bucket count is read here, not held across the loop
-                    const uint32_t nxt = b[q] + 1u == (uint32_t)MC_COLD(nb) ? 0u : b[q] + 1u;
-                    const uint32_t pos = (tail + rank_below(full)) & (kRing - 1u);
-                    ring[pos] = make_uint2(f[q], nxt);
-                    if (pos < kRingMirror) ring[pos + kRing] = make_uint2(f[q], nxt);
-                }
-                tail += popc64(full);
-            }
         }
+        // a group that did not find its feature in a full line goes on:
+        // found bits of the group's lanes together, the full bits from its
+        // last lane, lane 8g + 4 + q for step q
+        found |= xor_lanes<1>(found);
+        found |= xor_lanes<2>(found);
+        found |= (uint32_t)__builtin_amdgcn_mov_dpp((int)found, 0x141, 0xF, 0xF, false);  // half mirror
+        const uint32_t gf =
+            (uint32_t)__builtin_amdgcn_update_dpp(0, (int)fl, 0xFF, 0xF, 0xA, false) & ~found;
+        const uint64_t full = ballot(((gf >> l3) & 1u) != 0u);
+        if (full) requeue(a, full, batch, l3, ring, tail);
         if (nrun) {
             // lane r holds run r; an inclusive scan of the counts gives every
             // run's first list position
@@ -327,11 +388,14 @@ __device__ __forceinline__ void write_result(const QueryArgs& a, uint32_t rec, u
     uint32_t* const out_top = MC_COLD(out_top);
     const uint32_t top_m = MC_COLD(top_m);
     if (out_top && lane < top_m) {
+        // (opaque: the constants would be held in vector registers)
+        uint32_t none = kNone, zero = 0u;
+        asm volatile("" : "+v"(none), "+v"(zero));
         const bool h = lane < nsel;
         uint32_t* o = out_top + ((uint64_t)rec * top_m + lane) * 3;
-        o[0] = h ? L.sel_t[lane] : kNone;
-        o[1] = h ? L.sel_s[lane] : 0u;
-        o[2] = h ? L.sel_b[lane] : 0u;
+        o[0] = h ? L.sel_t[lane] : none;
+        o[1] = h ? L.sel_s[lane] : zero;
+        o[2] = h ? L.sel_b[lane] : zero;
     }
 }
 
@@ -342,7 +406,9 @@ __device__ __forceinline__ uint64_t div_by_S(const QueryArgs& a, uint64_t n) {
         const uint32_t x = (uint32_t)n, t = __umulhi(a.divS.m, x);
         return (t + ((x - t) >> a.divS.sh1)) >> a.divS.sh2;
     }
-    return n / a.S;
+    uint32_t S = a.S;
+    asm volatile("" : "+s"(S));   // its reciprocal is not prepared ahead
+    return n / S;
 }
 
 // Windows of a mate of len bases, and the windows of reference a fragment of
@@ -563,32 +629,44 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
     // does not change during the launch)
     typedef const __attribute__((address_space(4))) uint64_t ConstU64;
     ConstU64* const off = (ConstU64*)(uintptr_t)a.offsets;
-    uint64_t o0, o1, o2;
-    if (a.paired) {
-        o0 = off[2ull * rec]; o1 = off[2ull * rec + 1]; o2 = off[2ull * rec + 2];
-    } else {
-        o0 = off[rec]; o1 = off[rec + 1ull]; o2 = o1;
-    }
-    if (o1 < o0 || o2 < o1) {           // malformed record: nothing to classify
-        write_result(a, rec, kNone, L, 0);
-        return;
-    }
+    const uint32_t at0 = a.paired;
+    const uint64_t o0 = off[(uint64_t)rec << at0], o1 = off[((uint64_t)rec << at0) + 1];
+    const uint64_t o2 = at0 ? off[((uint64_t)rec << at0) + 2] : o1;
+    // one test for every record that is not to be classified: with both
+    // lengths and their sum below 2^31 and no wrap past 2^64 the offsets
+    // ascend and the record is shorter than 2^31 bytes
+    const uint64_t d0 = o1 - o0, d1 = o2 - o1;
     RecordSpan rs;
-    if (!record_span(a, o0, o1, o2, rs)) {
-        if (lane == 0) atomicAdd(&MC_COLD(counters)[kQTooLong], 1u);
+    rs.len[0] = (uint32_t)d0;
+    rs.len[1] = (uint32_t)d1;
+    const uint32_t len = rs.len[0] + rs.len[1];
+    if (__builtin_expect(((uint32_t)(d0 >> 32) | (uint32_t)(d1 >> 32) |
+                          ((rs.len[0] | rs.len[1] | len) >> 31)) != 0u ||
+                          (uint32_t)(o2 >> 32) < (uint32_t)(o0 >> 32), 0)) {
+        // malformed (nothing to classify), or too long for every pass
+        if (!(o1 < o0 || o2 < o1) && lane == 0) atomicAdd(&MC_COLD(counters)[kQTooLong], 1u);
         write_result(a, rec, kNone, L, 0);
         return;
     }
-    // the fragment: the record's length (below 2^31), or the insert size
-    // when that is longer and both mates are present
-    const uint32_t len = rs.len[0] + rs.len[1];
-    const uint32_t F = rs.len[0] > 0 && rs.len[1] > 0 && a.insert_size > len ? a.insert_size : len;
-    const uint32_t sws = fragment_sws32(a, F);
+    const uintptr_t first = (uintptr_t)(a.reads + o0);
+    rs.base = first & ~(uintptr_t)15;
+    rs.r0 = (uint32_t)first & 15u;
 
-    // windows of the record, mate 1's then mate 2's, sketched two at a time
-    uint32_t nws[2];
-    for (int sg = 0; sg < 2; ++sg)
-        nws[sg] = mate_windows32(a, rs.len[sg]);
+    // windows of the record, mate 1's then mate 2's, sketched two at a time,
+    // and the reference windows its fragment can touch: the fragment is the
+    // record's length, or the insert size when that is longer and both mates
+    // are present
+    uint32_t nws[2], sws;
+    nws[0] = mate_windows32(a, rs.len[0]);
+    nws[1] = 0u;
+    if (rs.len[1] == 0u) {
+        // ceil((len - k) / S) + 1 from floor((len - k) / S) + 1 windows
+        sws = nws[0] + (rs.len[0] > a.k && (nws[0] - 1u) * a.S != rs.len[0] - a.k ? 1u : 0u);
+        sws = max(sws, 1u);
+    } else {
+        nws[1] = mate_windows32(a, rs.len[1]);
+        sws = fragment_sws32(a, rs.len[0] > 0u ? max(MC_COLD(insert_size), len) : len);
+    }
     const uint32_t nwt = nws[0] + nws[1];
     uint32_t nlist = 0, nf = 0;
     // a record with more sketch elements than the list holds most likely
@@ -626,8 +704,7 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
                                          reinterpret_cast<uint32_t*>(L.sk.stage), nlist,
                                          ws.probes);
             else
-                fits = lookup<LCAP>(a, L.sk.feats, nf, L.ring, L.list, L.sk.scratch, nlist,
-                                    ws.probes);
+                fits = lookup<LCAP>(a, L.sk.feats, nf, L.ring, L.list, nlist, ws.probes);
             nf = 0;
         }
     }
@@ -837,7 +914,6 @@ __device__ __forceinline__ void large_lookup(const QueryArgs& a, LargeLds& L, ui
                                              uint32_t wave, uint32_t& probes) {
     constexpr int NB = 4;
     constexpr uint32_t kPerWave = kDeep ? 8u : 8u * NB;
-    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
     const uint32_t lane = (uint32_t)lane_id(), g = lane >> 3;
     const u64x2* slot2 = reinterpret_cast<const u64x2*>(a.table) + (lane & 7u);
     const uint32_t nb = (uint32_t)a.nb;
@@ -1413,7 +1489,6 @@ __device__ void classify_huge_record(const QueryArgs& a, uint32_t rec, const Hug
 
     // lookups: 8-lane groups walk one feature's chain each, appending its
     // locations with an LDS counter
-    typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
     const u64x2* slot2 = reinterpret_cast<const u64x2*>(a.table) + (lane & 7u);
     const uint32_t nb = (uint32_t)a.nb;
     uint32_t probes = 0;
