@@ -75,6 +75,7 @@ struct Workspace {
     unsigned long long* qstats = nullptr;    // kQsWords
     unsigned char* huge = nullptr;           // kHugeBytes (HBM-list pass)
     uint32_t huge_groups = 0;                // regions in huge (0 = kHugeGroups)
+    bool recount = false;                    // the queue counts may not be zero (a launch failed)
 };
 
 
@@ -767,11 +768,7 @@ int init_workspace(Workspace& w, hipStream_t st) {
     if (int rc = dev_alloc(&w.qstats, kQsWords)) return rc;
     if (int rc = dev_alloc(&w.huge, kHugeBytes)) return rc;
     if (int rc = dev_alloc(&w.route_meta, kRouteMetaWords)) return rc;
-    HIP_TRY(launch_fill_u32(w.counters, kNumQueryCounters, 0u, st));
-    HIP_TRY(launch_fill_u64(w.qstats, kQsWords, 0ull, st));
-    for (uint32_t r = 0; r < kHugeGroups; ++r)
-        HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(w.huge + r * kHugeRegionBytes),
-                                kHugeTargets, 0ull, st));
+    HIP_TRY(launch_clear_workspace(w.counters, w.huge, kHugeGroups, w.qstats, st));
     return MC_OK;
 }
 
@@ -879,11 +876,22 @@ int classify_launch(mc_db* db, const char* reads, const uint64_t* offsets, uint3
                     const mc_query_opts& opts, uint32_t* out_labels, mc_tophit* out_top,
                     Workspace& w, const LaunchPlan& plan, hipStream_t st, bool profile) {
     static_assert(kQOverflow == 0 && kQHuge == 1, "the per-launch queue counters lead");
-    HIP_TRY(launch_fill_u32(w.counters, 2, 0u, st));
+    // the passes leave the queue counts at zero; cleared here only after a
+    // sequence of launches that did not reach the last pass
+    if (w.recount) {
+        HIP_TRY(launch_fill_u32(w.counters, 2, 0u, st));
+        HIP_TRY(launch_fill_u32(w.counters + kQDone, 1, 0u, st));
+    }
+    const bool was = w.recount;
+    w.recount = true;
     const QueryArgs a = query_args(db, reads, offsets, n_records, opts, out_labels, out_top, w);
     if (int rc = launch_fast_phase(db, a, w, plan, st, profile)) return rc;
     HIP_TRY(launch_classify_large(a, st, 0));
     HIP_TRY(launch_classify_huge(a, st));
+    // a clearing that was only captured has not run yet
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    w.recount = was && (hipStreamIsCapturing(st, &cap) != hipSuccess ||
+                        cap != hipStreamCaptureStatusNone);
     return MC_OK;
 }
 
@@ -1003,10 +1011,7 @@ int classify_into(struct ::mc_db* db, const char* reads, const uint64_t* offsets
     w.huge = scratch.huge;
     w.huge_groups = scratch.huge_groups;
     // what the passes expect at zero: the counters and the per-target bests
-    HIP_TRY(launch_fill_u32(w.counters, kNumQueryCounters, 0u, st));
-    for (uint32_t r = 0; r < scratch.huge_groups; ++r)
-        HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(w.huge + r * kHugeRegionBytes),
-                                kHugeTargets, 0ull, st));
+    HIP_TRY(launch_clear_workspace(w.counters, w.huge, scratch.huge_groups, nullptr, st));
     return classify_launch(db, reads, offsets, n_records, *opts, out_labels, out_top, w, db->plan,
                            st, false);
 }

@@ -109,6 +109,7 @@ enum QueryCounter {
     kQOverflow = 0,      // records queued for the large-list pass
     kQHuge = 1,          // records queued for the HBM-list pass
     kQTooLong = 2,       // records beyond every pass's capacity (left unclassified)
+    kQDone = 3,          // workgroups of the HBM-list pass that read the counts above
     kNumQueryCounters = 4
 };
 
@@ -273,6 +274,11 @@ hipError_t launch_rehash(const unsigned long long* old_table, uint64_t old_nb,
 hipError_t launch_fill_u64(unsigned long long* p, uint64_t n, unsigned long long v,
                            hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t st);
+// Zero what the query passes expect at zero in one launch: the counters, the
+// per-target bests of `regions` regions of the HBM-list scratch and, unless
+// null, the work statistics.
+hipError_t launch_clear_workspace(uint32_t* counters, unsigned char* huge, uint32_t regions,
+                                  unsigned long long* qstats, hipStream_t st);
 hipError_t launch_dump(const unsigned long long* table, uint64_t nb, uint32_t lo, uint32_t hi,
                        unsigned long long* out, uint64_t cap, unsigned long long* count,
                        hipStream_t st);

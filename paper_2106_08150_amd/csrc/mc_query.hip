@@ -137,7 +137,7 @@ __device__ __forceinline__ bool lookup_batch(const QueryArgs& a, const u64x2* sl
     // much as vector, so hits are counted a lane and placed by one prefix sum
     // a batch; a wave's hit masks in scalar registers took 15 scalar
     // instructions a slot and step more. With the requeue once a batch and the
-    // shorter record header, 10M reads of 150 bases on 1 Gbp: 757 -> 619
+    // shorter record header, 10M reads of 150 bases on 4 Gbp: 757 -> 619
     // scalar instructions a read, 14.84 -> 13.5 ms (385M random lines alone
     // would take 10 ms).
     uint32_t nh = 0, fl = 0;
@@ -206,7 +206,7 @@ __device__ bool lookup(const QueryArgs& a, const uint32_t* F, uint32_t nf, uint2
         probes += c;
         // a whole batch (two full windows of a read) needs no masks; a batch
         // of at most a line a group (mostly second buckets of chains) takes
-        // one step: 14.0 -> 13.5 ms for 10M reads of 150 bases on 1 Gbp
+        // one step: 14.0 -> 13.5 ms for 10M reads of 150 bases on 4 Gbp
         bool fits;
         if (c == kGroups * kBatchSteps)
             fits = lookup_batch<LCAP, kBatchSteps, true>(a, slot2, batch, c, l3, ring, list, nlist,
@@ -1655,11 +1655,31 @@ __device__ void classify_huge_record(const QueryArgs& a, uint32_t rec, const Hug
 template <int KPL, bool C>
 __global__ __launch_bounds__(kHugeThreads) void k_classify_huge(QueryArgs a) {
     __shared__ HugeLds L;
+    if (uniform(a.counters[kQOverflow]) == 0u) return;   // nothing was passed on
     const uint32_t n_iter = uniform(a.counters[kQHuge]);
     const HugeRegion h = huge_region(a.huge, blockIdx.x);
     const Threshold th(a.S, a.s);
     for (uint32_t it = blockIdx.x; it < n_iter; it += gridDim.x)
         classify_huge_record<KPL, C>(a, uniform(a.queue[a.n_records + it]), h, L, th);
+    // the last workgroup sets the queue counts back for the next classification
+    // with this workspace (a launch that cleared them first: 20.4 against 16.7
+    // us for a call of 200 reads, 29.6 against 24.0 us for a graph of 3,001)
+    if (threadIdx.x == 0 && atomicAdd(&a.counters[kQDone], 1u) + 1u == gridDim.x) {
+        a.counters[kQOverflow] = 0u;
+        a.counters[kQHuge] = 0u;
+        a.counters[kQDone] = 0u;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_clear_workspace(uint32_t* counters, unsigned char* huge,
+                                                         uint32_t regions,
+                                                         unsigned long long* qstats) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i < kNumQueryCounters) counters[i] = 0u;
+    if (qstats && i < kQsWords) qstats[i] = 0ull;
+    if (i < regions * kHugeTargets)
+        reinterpret_cast<unsigned long long*>(huge + (i / kHugeTargets) *
+                                              kHugeRegionBytes)[i % kHugeTargets] = 0ull;
 }
 
 template <uint32_t LCAP, int WPB, int KPL, bool C>
@@ -1812,6 +1832,14 @@ hipError_t launch_route(const QueryArgs& a, const RouteConfig& r, hipStream_t st
 hipError_t launch_classify_class(const QueryArgs& a, const ClassifyConfig& c, uint32_t cls,
                                  hipStream_t st) {
     return launch_fast_any(a, c, (int)cls, st);
+}
+
+hipError_t launch_clear_workspace(uint32_t* counters, unsigned char* huge, uint32_t regions,
+                                  unsigned long long* qstats, hipStream_t st) {
+    static_assert(kQsWords <= kHugeTargets && kNumQueryCounters <= 256, "covered by one region's threads");
+    hipLaunchKernelGGL(k_clear_workspace, dim3(std::max(regions, 1u) * (kHugeTargets / 256)),
+                       dim3(256), 0, st, counters, huge, regions, qstats);
+    return hipGetLastError();
 }
 
 hipError_t launch_classify_huge(const QueryArgs& a, hipStream_t st) {
