@@ -875,19 +875,19 @@ int launch_fast_phase(mc_db* db, const QueryArgs& a, Workspace& w, const LaunchP
 int classify_launch(mc_db* db, const char* reads, const uint64_t* offsets, uint32_t n_records,
                     const mc_query_opts& opts, uint32_t* out_labels, mc_tophit* out_top,
                     Workspace& w, const LaunchPlan& plan, hipStream_t st, bool profile) {
-    static_assert(kQOverflow == 0 && kQHuge == 1, "the per-launch queue counters lead");
+    static_assert(kQOverflow == 0 && kQHuge == 1 && kQTooLong == 2 && kQDone == 3,
+                  "all counters but kQTooLong are a launch's own");
     // the passes leave the queue counts at zero; cleared here only after a
     // sequence of launches that did not reach the last pass
     if (w.recount) {
         HIP_TRY(launch_fill_u32(w.counters, 2, 0u, st));
-        HIP_TRY(launch_fill_u32(w.counters + kQDone, 1, 0u, st));
+        HIP_TRY(launch_fill_u32(w.counters + kQDone, kNumQueryCounters - kQDone, 0u, st));
     }
     const bool was = w.recount;
     w.recount = true;
     const QueryArgs a = query_args(db, reads, offsets, n_records, opts, out_labels, out_top, w);
     if (int rc = launch_fast_phase(db, a, w, plan, st, profile)) return rc;
     HIP_TRY(launch_classify_large(a, st, 0));
-    HIP_TRY(launch_classify_huge(a, st));
     // a clearing that was only captured has not run yet
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     w.recount = was && (hipStreamIsCapturing(st, &cap) != hipSuccess ||
@@ -1036,11 +1036,7 @@ int served_classify(struct ::mc_db* db, int phase, const char* reads, const uint
         HIP_TRY(launch_fill_u32(counters, kNumQueryCounters, 0u, st));
         return launch_fast_phase(db, a, w, db->plan, st, db->profiling);
     }
-    if (phase == 1) {
-        HIP_TRY(launch_classify_large(a, st, n_queued));
-        return MC_OK;
-    }
-    HIP_TRY(launch_classify_huge(a, st));
+    HIP_TRY(launch_classify_large(a, st, n_queued));
     return MC_OK;
 }
 

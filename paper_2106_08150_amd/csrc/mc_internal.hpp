@@ -107,15 +107,18 @@ inline uint32_t scatter_chunk_tiles(uint32_t s) {
 // Query-side counters (device, u32).
 enum QueryCounter {
     kQOverflow = 0,      // records queued for the large-list pass
-    kQHuge = 1,          // records queued for the HBM-list pass
+    kQHuge = 1,          // records queued for the HBM-list path (places taken in its queue)
     kQTooLong = 2,       // records beyond every pass's capacity (left unclassified)
-    kQDone = 3,          // workgroups of the HBM-list pass that read the counts above
-    kNumQueryCounters = 4
+    kQDone = 3,          // workgroups of the large-list pass that have finished
+    kQHugeReady = 4,     // records written to the HBM-list queue
+    kQHugeNext = 5,      // records taken from it
+    kQHugeBusy = 6,      // regions of the HBM-list scratch in use (bit mask)
+    kNumQueryCounters = 8
 };
 
-// HBM-list pass: one workgroup a record, its lists in device memory. Each of
-// kHugeGroups workgroups owns one region of the workspace's huge scratch.
-constexpr int kHugeThreads = 256;
+// HBM-list path: one workgroup of the large-list pass a record, its lists in
+// device memory, in one of the kHugeGroups regions of the workspace's huge
+// scratch.
 constexpr uint32_t kHugeGroups = 4;
 constexpr uint32_t kHugeFeats = 1u << 14;      // sketch elements of one record
 constexpr uint32_t kHugeLocs = 1u << 20;       // candidate locations of one record
@@ -166,7 +169,7 @@ struct QueryArgs {
     unsigned long long* qstats;   // kQsWords: kQsCopies partial totals (or null)
     unsigned char* huge;          // HBM-list scratch: huge_groups regions of kHugeRegionBytes
                                   // (per-target bests zero)
-    uint32_t huge_groups;         // regions (workgroups of the HBM-list pass), 0 = kHugeGroups
+    uint32_t huge_groups;         // regions, 0 = kHugeGroups
     // condensed layout (when cval is set): `table` holds nb index buckets of
     // kCondEntries 16-byte entries, and cval the runs of locations
     const uint32_t* cval;
@@ -300,7 +303,8 @@ struct ClassifyConfig {
 bool classify_config_valid(const ClassifyConfig& c);
 
 // Fast path (one wave per record, small LDS list) and the large-list pass
-// over the records the fast path queued.
+// over the records the fast path queued (with the HBM-list path of those whose
+// list outgrows it).
 hipError_t launch_classify_fast(const QueryArgs& a, const ClassifyConfig& c, hipStream_t st);
 // groups: workgroups of the large-list pass (0: sized by the launch's records).
 hipError_t launch_classify_large(const QueryArgs& a, hipStream_t st, uint32_t groups);
@@ -309,7 +313,6 @@ hipError_t launch_classify_large(const QueryArgs& a, hipStream_t st, uint32_t gr
 hipError_t launch_route(const QueryArgs& a, const RouteConfig& r, hipStream_t st);
 hipError_t launch_classify_class(const QueryArgs& a, const ClassifyConfig& c, uint32_t cls,
                                  hipStream_t st);
-hipError_t launch_classify_huge(const QueryArgs& a, hipStream_t st);
 // Condensed layout build: the count pass (totals in c.res, prefix of the run
 // values), and the write pass (runs and index entries; most: the count pass's).
 hipError_t launch_condense_count(CondArgs c, hipStream_t st);
@@ -350,14 +353,13 @@ int classify_into(struct ::mc_db* db, const char* reads, const uint64_t* offsets
                   struct mc_tophit* out_top, const ScratchView& scratch, hipStream_t st);
 
 // Classification of the records [r0, r1) of a served batch (offsets: the
-// batch's offsets array) in three phases, each queued on st: phase 0 clears
+// batch's offsets array) in two phases, each queued on st: phase 0 clears
 // `counters` (kNumQueryCounters u32 of device memory owned by the caller) and
 // queues the fast pass; phase 1 the large-list pass over the n_queued records
-// the fast pass passed on (counters[kQOverflow]); phase 2 the HBM-list pass
-// over those the large-list pass passed on (counters[kQHuge]). The caller
-// reads the counters back and queues phases 1 and 2 only when they hold
-// records: a large-list workgroup needs a CU of its own, which a busy device
-// frees only when its other kernels drain. The records' queue ids sit at
+// the fast pass passed on (counters[kQOverflow]). The caller reads the counters
+// back and queues phase 1 only when they hold records: a large-list workgroup
+// takes half of a CU's LDS, which a busy device frees only when its other
+// kernels drain. The records' queue ids sit at
 // 2 r0 .. 2 r1 of st's workspace queue, which prepare_workspace must have
 // sized for r1 records.
 int served_classify(struct ::mc_db* db, int phase, const char* reads, const uint64_t* offsets,

@@ -26,6 +26,24 @@ __device__ __forceinline__ T arg_at_use(uint32_t off) {
         (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
     return *(const __attribute__((address_space(4))) T*)(base + off);
 }
+// All of the arguments, read here.
+template <typename T>
+__device__ __forceinline__ T args_at_use() {
+    constexpr uint32_t n = sizeof(T) / 4;
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[n];
+    uint32_t off = 0;
+    asm volatile("" : "+s"(off));
+    const __attribute__((address_space(4))) char* base =
+        (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+    const __attribute__((address_space(4))) uint32_t* p =
+        (const __attribute__((address_space(4))) uint32_t*)(base + off);
+#pragma unroll
+    for (uint32_t i = 0; i < n; ++i) w[i] = p[i];
+    T t;
+    __builtin_memcpy(&t, w, sizeof t);
+    return t;
+}
 #define MC_COLD(field) arg_at_use<decltype(QueryArgs::field)>((uint32_t)offsetof(QueryArgs, field))
 
 constexpr int kStageWords = 20;    // one window of at most 271 bases (19 words)
@@ -890,7 +908,7 @@ struct LargeLds {
     uint32_t nfeat, nlist;
     uint32_t sel_t[kMaxTopM], sel_s[kMaxTopM], sel_b[kMaxTopM];
 };
-static_assert(sizeof(LargeLds) <= 80 * 1024, "two workgroups a CU");
+static_assert(sizeof(LargeLds) + 16 <= 80 * 1024, "two workgroups a CU");
 
 // Place of list entry i: the low five index bits are swapped around by the
 // next five, so that neither the lanes' runs of consecutive entries (the
@@ -1313,10 +1331,13 @@ __device__ void classify_large_record(const QueryArgs& a, uint32_t rec, LargeLds
     }
     __syncthreads();
     const uint32_t n = uniform(L.nlist);
-    if (n > kListLarge) {                  // queued for the HBM-list pass (ids from n_records on)
+    if (n > kListLarge) {                  // queued for the HBM-list path (ids from n_records on)
         if (tid == 0) {
-            const uint32_t qi = atomicAdd(&a.counters[kQHuge], 1u);
+            const uint32_t qi = atomicAdd(&MC_COLD(counters)[kQHuge], 1u);
             a.queue[a.n_records + qi] = rec;
+            __threadfence();
+            atomicAdd(&MC_COLD(counters)[kQHugeReady], 1u);
+            __threadfence();
             ws.passed_on += 1;
         }
         return;
@@ -1329,30 +1350,9 @@ __device__ void classify_large_record(const QueryArgs& a, uint32_t rec, LargeLds
     else large_rank<32>(a, L, rec, n, sws);
 }
 
-template <int KPL, bool C>
-__global__ __launch_bounds__(kLargeThreads) __attribute__((amdgpu_waves_per_eu(4)))
-void k_classify_large(QueryArgs a) {
-    __shared__ LargeLds L;
-    const uint32_t n_iter = uniform(a.counters[kQOverflow]);
-    if (blockIdx.x >= n_iter) return;
-    WaveStats ws;
-    const Threshold th(a.S, a.s);
-    for (uint32_t it = blockIdx.x; it < n_iter; it += gridDim.x)
-        classify_large_record<KPL, C>(a, uniform(a.queue[it]), L, th, ws);
-    // work of records that go on to the HBM-list pass counts in both passes
-    if (lane_id() == 0 && a.qstats) {
-        unsigned long long* q =
-            a.qstats + ((blockIdx.x * kLargeWaves + (threadIdx.x >> 6)) % kQsCopies) * kQsStride;
-        if (ws.features) atomicAdd(&q[kQsFeatures], (unsigned long long)ws.features);
-        if (ws.locations) atomicAdd(&q[kQsLocations], (unsigned long long)ws.locations);
-        if (ws.probes) atomicAdd(&q[kQsProbes], (unsigned long long)ws.probes);
-        if (ws.passed_on) atomicAdd(&q[kQsHuge], (unsigned long long)ws.passed_on);
-    }
-}
-
-// ------------------------------------------------------ HBM-list pass -----
+// ------------------------------------------------------ HBM-list path -----
 // Records whose candidate list outgrew the large-list pass: one workgroup a
-// record, the lists in its region of the workspace's huge scratch. The steps
+// record, the lists in a region of the workspace's huge scratch. The steps
 // are those of the other passes (Sec. 4.2, Sec. 5.3-5.6) without a sort: the
 // window count of each distinct location is accumulated in a hash table in
 // HBM (Q4-Q6), the score of the range of `sws` windows starting at each
@@ -1404,7 +1404,7 @@ __device__ __forceinline__ uint32_t huge_count(const HugeRegion& h, uint32_t mas
     }
 }
 
-constexpr int kHugeWaves = kHugeThreads / kWave;
+constexpr int kHugeThreads = kLargeThreads, kHugeWaves = kLargeWaves;
 
 struct HugeLds {
     Word stage[kHugeWaves][2 * kStageWords];
@@ -1650,25 +1650,106 @@ __device__ void classify_huge_record(const QueryArgs& a, uint32_t rec, const Hug
     __syncthreads();
 }
 
-// Workgroup r uses region r of the huge scratch and takes records r,
-// r + kHugeGroups, ... of the HBM-list queue (its ids start at n_records).
-template <int KPL, bool C>
-__global__ __launch_bounds__(kHugeThreads) void k_classify_huge(QueryArgs a) {
-    __shared__ HugeLds L;
-    if (uniform(a.counters[kQOverflow]) == 0u) return;   // nothing was passed on
-    const uint32_t n_iter = uniform(a.counters[kQHuge]);
-    const HugeRegion h = huge_region(a.huge, blockIdx.x);
-    const Threshold th(a.S, a.s);
-    for (uint32_t it = blockIdx.x; it < n_iter; it += gridDim.x)
-        classify_huge_record<KPL, C>(a, uniform(a.queue[a.n_records + it]), h, L, th);
-    // the last workgroup sets the queue counts back for the next classification
-    // with this workspace (a launch that cleared them first: 20.4 against 16.7
-    // us for a call of 200 reads, 29.6 against 24.0 us for a graph of 3,001)
-    if (threadIdx.x == 0 && atomicAdd(&a.counters[kQDone], 1u) + 1u == gridDim.x) {
-        a.counters[kQOverflow] = 0u;
-        a.counters[kQHuge] = 0u;
-        a.counters[kQDone] = 0u;
+// The next record of the HBM-list queue, or kNone (one thread). Records are
+// taken only while every place given out in the queue has been written: a
+// workgroup that is queuing one comes here itself once it is done.
+__device__ __forceinline__ uint32_t take_huge(const QueryArgs& a) {
+    uint32_t* const c = a.counters;
+    for (;;) {
+        const uint32_t ready =
+            __hip_atomic_load(&c[kQHugeReady], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+        if (ready != ld_dev(&c[kQHuge])) return kNone;
+        const uint32_t next = ld_dev(&c[kQHugeNext]);
+        if (next >= ready) return kNone;
+        if (atomicCAS(&c[kQHugeNext], next, next + 1u) == next) {
+            __threadfence();
+            return ld_dev(&a.queue[a.n_records + next]);
+        }
     }
+}
+
+// A free region of the huge scratch while records are queued, or kNone (one
+// thread; no waiting).
+__device__ __forceinline__ uint32_t take_region(const QueryArgs& a) {
+    if (ld_dev(&a.counters[kQHugeNext]) >= ld_dev(&a.counters[kQHugeReady])) return kNone;
+    const uint32_t n = a.huge_groups ? a.huge_groups : kHugeGroups;
+    for (uint32_t r = 0; r < n; ++r)
+        if (!(atomicOr(&a.counters[kQHugeBusy], 1u << r) >> r & 1u)) return r;
+    return kNone;
+}
+
+// Large-list pass and, in the same launch, the HBM-list path: a workgroup that
+// is through with its records takes a free region and works on the HBM-list
+// queue until it is empty. The last of the workgroups does so when all the
+// others have finished, so that no record is left, and then sets the counts
+// back for the next classification with this workspace. Nothing waits. As
+// launches of their own, the HBM-list path and a clearing of the counts took
+// about 3 us each: a call of 200 reads 20.4 -> 13.7 us, of 10,000 reads 25.4 ->
+// 21.8 us, a graph of 3,001 records 29.6 -> 22.0 us.
+template <int KPL, bool C>
+__global__ __launch_bounds__(kLargeThreads) __attribute__((amdgpu_waves_per_eu(4)))
+void k_classify_large(QueryArgs a) {
+    __shared__ union {
+        LargeLds large;
+        HugeLds huge;
+    } L;
+    __shared__ uint32_t s_job;
+    const uint32_t n_iter = uniform(a.counters[kQOverflow]);
+    if (blockIdx.x >= n_iter) return;
+    const Threshold th(a.S, a.s);
+    {
+        WaveStats ws;
+        for (uint32_t it = blockIdx.x; it < n_iter; it += gridDim.x)
+            classify_large_record<KPL, C>(a, uniform(a.queue[it]), L.large, th, ws);
+        // work of records that go on to the HBM-list path counts in both
+        if (lane_id() == 0 && a.qstats) {
+            unsigned long long* q =
+                a.qstats + ((blockIdx.x * kLargeWaves + (threadIdx.x >> 6)) % kQsCopies) * kQsStride;
+            if (ws.features) atomicAdd(&q[kQsFeatures], (unsigned long long)ws.features);
+            if (ws.locations) atomicAdd(&q[kQsLocations], (unsigned long long)ws.locations);
+            if (ws.probes) atomicAdd(&q[kQsProbes], (unsigned long long)ws.probes);
+            if (ws.passed_on) atomicAdd(&q[kQsHuge], (unsigned long long)ws.passed_on);
+        }
+    }
+    const uint32_t groups = min(gridDim.x, n_iter);   // workgroups with records
+    for (bool last = false;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) s_job = take_region(a);
+        __syncthreads();
+        const uint32_t region = uniform(s_job);
+        if (region != kNone) {
+            __threadfence();           // the region as its last user left it
+            const QueryArgs b = args_at_use<QueryArgs>();   // (not kept from before)
+            const HugeRegion h = huge_region(b.huge, region);
+            const Threshold th2(b.S, b.s);
+            for (;;) {
+                __syncthreads();
+                if (threadIdx.x == 0) s_job = take_huge(b);
+                __syncthreads();
+                const uint32_t rec = uniform(s_job);
+                if (rec == kNone) break;
+                classify_huge_record<KPL, C>(b, rec, h, L.huge, th2);
+            }
+            __threadfence();
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                atomicAnd(&a.counters[kQHugeBusy], ~(1u << region));
+                __threadfence();
+            }
+        }
+        if (last) break;
+        __syncthreads();               // s_job has been read by all
+        // (what this workgroup queued or gave back is ordered before this by
+        // the fences there)
+        if (threadIdx.x == 0) {
+            s_job = atomicAdd(&a.counters[kQDone], 1u) + 1u == groups ? 1u : 0u;
+            if (s_job) __threadfence();
+        }
+        __syncthreads();
+        if (!uniform(s_job)) return;
+        last = true;
+    }
+    if (threadIdx.x < kNumQueryCounters && threadIdx.x != kQTooLong) a.counters[threadIdx.x] = 0u;
 }
 
 __global__ __launch_bounds__(256) void k_clear_workspace(uint32_t* counters, unsigned char* huge,
@@ -1839,21 +1920,6 @@ hipError_t launch_clear_workspace(uint32_t* counters, unsigned char* huge, uint3
     static_assert(kQsWords <= kHugeTargets && kNumQueryCounters <= 256, "covered by one region's threads");
     hipLaunchKernelGGL(k_clear_workspace, dim3(std::max(regions, 1u) * (kHugeTargets / 256)),
                        dim3(256), 0, st, counters, huge, regions, qstats);
-    return hipGetLastError();
-}
-
-hipError_t launch_classify_huge(const QueryArgs& a, hipStream_t st) {
-    if (a.n_records == 0) return hipSuccess;
-    const dim3 grid(a.huge_groups ? a.huge_groups : kHugeGroups), blk(kHugeThreads);
-    if (a.cval) {
-        if (a.S <= 64) hipLaunchKernelGGL((k_classify_huge<1, true>), grid, blk, 0, st, a);
-        else if (a.S <= 128) hipLaunchKernelGGL((k_classify_huge<2, true>), grid, blk, 0, st, a);
-        else hipLaunchKernelGGL((k_classify_huge<4, true>), grid, blk, 0, st, a);
-    } else {
-        if (a.S <= 64) hipLaunchKernelGGL((k_classify_huge<1, false>), grid, blk, 0, st, a);
-        else if (a.S <= 128) hipLaunchKernelGGL((k_classify_huge<2, false>), grid, blk, 0, st, a);
-        else hipLaunchKernelGGL((k_classify_huge<4, false>), grid, blk, 0, st, a);
-    }
     return hipGetLastError();
 }
 

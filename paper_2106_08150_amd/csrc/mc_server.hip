@@ -239,9 +239,9 @@ struct mc_server {
     //
     // Each chunk's fast pass counts the records it passes on in counters of
     // its own; they come back with the results, and only chunks that passed
-    // records on get the large-list pass (then, the same way, the HBM-list
-    // pass). A large-list workgroup takes most of a CU's LDS and starts only
-    // on a CU that every other kernel has left: queued unconditionally next
+    // records on get the large-list pass. A large-list workgroup takes half of
+    // a CU's LDS and starts only on a CU that other kernels have left so far:
+    // queued unconditionally next
     // to other batches' kernels, it would hold up every batch until the
     // device drains.
     int process(Slot& s, Job& j) {
@@ -340,19 +340,15 @@ struct mc_server {
             (void)hipEventElapsedTime(&j.gpu_kernels_ms, s.t_kernels, s.t_kernels_done);
             (void)hipEventElapsedTime(&j.gpu_copy_back_ms, s.t_kernels_done, s.t_back);
         }
-        // the passes for records with long candidate lists, where there are any
-        for (int phase = 1; phase <= 2; ++phase) {
-            const int which = phase == 1 ? mc::kQOverflow : mc::kQHuge;
-            bool any = false;
-            for (uint32_t c = 0; c < n_chunks; ++c) {
-                const uint32_t q = chunk_cnt(c, which);
-                if (!q) continue;
-                any = true;
-                if ((rc = classify(phase, c, q)) != MC_OK) return rc;
-            }
-            if (!any) break;
-            if ((rc = copy_back()) != MC_OK) return rc;
+        // the pass for records with long candidate lists, where there are any
+        bool any = false;
+        for (uint32_t c = 0; c < n_chunks; ++c) {
+            const uint32_t q = chunk_cnt(c, mc::kQOverflow);
+            if (!q) continue;
+            any = true;
+            if ((rc = classify(1, c, q)) != MC_OK) return rc;
         }
+        if (any && (rc = copy_back()) != MC_OK) return rc;
         std::memcpy(j.out_labels, s.h_buf + off_labels, (size_t)j.n * 4);
         if (j.out_top) std::memcpy(j.out_top, s.h_buf + off_top, top_bytes);
         return MC_OK;
