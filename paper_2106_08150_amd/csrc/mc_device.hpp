@@ -337,83 +337,87 @@ __device__ __forceinline__ bool kmer_at(const Word* W, uint32_t x, uint32_t k, u
 }
 
 // ------------------------------------------------------- bitonic in regs --
-// Lanes of a compare-exchange step of a bitonic network that keep the smaller
-// key: those whose block of `size` runs ascending ((element & size) == 0) and
-// that are the lower partner ((lane & stride) == 0), or neither. The elements
-// are r * 64 + lane, or, for two independent 32-lane networks (halves), lane
-// & 31. A constant of the step.
-__host__ __device__ constexpr uint64_t keep_low_lanes(int size, int stride, int r,
-                                                      bool halves = false) {
-    uint64_t m = 0;
-    for (int l = 0; l < 64; ++l) {
-        const int e = halves ? (l & 31) : r * 64 + l;
-        const bool asc = (e & size) == 0;
-        const bool lower = (l & stride) == 0;
-        if (asc == lower) m |= 1ull << l;
-    }
-    return m;
-}
-static_assert(keep_low_lanes(2, 1, 0) == 0x9999999999999999ull, "first step: up, down, ...");
-static_assert(keep_low_lanes(64, 32, 0) == 0x00000000FFFFFFFFull, "last merge runs ascending");
-static_assert(keep_low_lanes(64, 1, 1) == 0xAAAAAAAAAAAAAAAAull, "second register descends");
-static_assert(keep_low_lanes(32, 16, 0, true) == 0x0000FFFF0000FFFFull,
-              "both halves' last merge runs ascending");
-static_assert(keep_low_lanes(16, 8, 0, true) == keep_low_lanes(16, 8, 0), "halves agree below 32");
+// Ascending networks on keys held one a lane (element = lane) and K a lane
+// (element = r * 64 + lane). A phase of `size` first exchanges each element with
+// its mirror in the block (e ^ (size - 1)), then at strides size / 4 .. 1; the
+// lower partner always keeps the smaller key, so no step has a direction. A
+// phase over several registers has none to mirror across cheaply: there the
+// odd blocks are sorted descending, as ascending blocks of complemented keys.
+//
+// A step is a lane exchange and one median of three: the median of two keys
+// and 0 is the smaller, that of two keys and all ones the larger. Minimum,
+// maximum and a select by a mask of constants took one vector and two scalar
+// instructions more a step: 10M reads of 150 bases on 4 Gbp 13.5 -> 12.55 ms
+// (692 -> 650 vector and 619 -> 526 scalar instructions a read), the sketches
+// of 4 Gbp 7.1 -> 6.4 ms.
 
-// Compile-time check of the step masks: the networks of wave_sort (KPL keys a
-// lane) and wave_sort_halves, run on the host over a few key patterns with
-// these masks, leave every sequence ascending.
+// All ones in the lanes with bit m (a power of two) of the lane id set.
+__device__ __forceinline__ uint32_t high_lanes(uint32_t lane, int m) {
+    return 0u - (lane / (uint32_t)m & 1u);
+}
+
+// The smaller of two keys where high is 0, the larger where it is all ones.
+__device__ __forceinline__ uint32_t keep_of(uint32_t v, uint32_t o, uint32_t high) {
+    return max(min(v, o), min(max(v, o), high));
+}
+
+// Value of lane (lane ^ (size - 1)): DPP permutes up to the 16-lane row,
+// ds_swizzle for 32 and a backwards permute for the wave.
+__device__ __forceinline__ uint32_t mirror_lanes(uint32_t v, int size) {
+    switch (size) {
+        case 2: return xor_lanes<1>(v);
+        case 4: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x1B, 0xF, 0xF, true);
+        case 8: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);
+        case 16: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);
+        case 32: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (0x1F << 10) | 0x1F);
+        default: return shfl_idx(v, 63 - lane_id());
+    }
+}
+
+// Compile-time check: the networks of wave_sort (KPL keys a lane) and
+// wave_sort_halves, run on the host over a few key patterns, leave every
+// sequence ascending.
 template <int KPL>
-constexpr bool bitonic_masks_sort(bool halves, uint32_t seed) {
+constexpr bool networks_sort(int top, uint32_t seed) {
     constexpr int N = 64 * KPL;
     uint32_t v[N] = {};
     for (int e = 0; e < N; ++e) v[e] = ((uint32_t)e * 2654435761u + seed) % 97u;   // duplicates too
-    const int top = halves ? 32 : N;
-    for (int size = 2; size <= top; size <<= 1)
+    for (int size = 2; size <= top; size <<= 1) {
+        const bool flips = size >= 64 && size < N;         // odd blocks descend
+        for (int e = 0; e < N; ++e)
+            if (flips && (e & size)) v[e] = ~v[e];
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            uint64_t mask[KPL] = {};
-            for (int r = 0; r < KPL && stride < 64; ++r)
-                mask[r] = keep_low_lanes(size, stride, r, halves);
+            const bool mirror = stride == size >> 1 && size <= 64;
             uint32_t nv[N] = {};
             for (int e = 0; e < N; ++e) {
-                const int r = e / 64, l = e % 64;
-                const uint32_t o = v[e ^ stride];
-                const uint32_t lo = v[e] < o ? v[e] : o, hi = v[e] < o ? o : v[e];
-                const bool low = stride >= 64
-                                     ? ((((r * 64) & size) == 0) == ((e & stride) == 0))
-                                     : ((mask[r] >> l) & 1u) != 0;
-                nv[e] = low ? lo : hi;
+                const uint32_t o = v[mirror ? e ^ (size - 1) : e ^ stride];
+                const bool low = (e & stride) == 0;
+                nv[e] = low ? (v[e] < o ? v[e] : o) : (v[e] < o ? o : v[e]);
             }
             for (int e = 0; e < N; ++e) v[e] = nv[e];
         }
+        for (int e = 0; e < N; ++e)
+            if (flips && (e & size)) v[e] = ~v[e];
+    }
     for (int e = 1; e < N; ++e)
-        if ((!halves || (e & 31) != 0) && v[e - 1] > v[e]) return false;
+        if (e % top != 0 && v[e - 1] > v[e]) return false;
     return true;
 }
-static_assert(bitonic_masks_sort<1>(false, 0) && bitonic_masks_sort<1>(false, 5),
-              "64-key network");
-static_assert(bitonic_masks_sort<2>(false, 1) && bitonic_masks_sort<4>(false, 3),
-              "128- and 256-key networks");
-static_assert(bitonic_masks_sort<1>(true, 0) && bitonic_masks_sort<1>(true, 7),
-              "two 32-key networks");
-
-// The lanes of a constant 64-bit mask as a per-lane predicate. The mask is
-// written by two scalar moves of immediates where it is used (volatile, so
-// they are not hoisted): a mask computed once outside the enclosing loops
-// would stay live in scalar registers across them and be spilled.
-__device__ __forceinline__ bool lanes_of(uint64_t mask) {
-    uint32_t lo, hi;
-    asm volatile("s_mov_b32 %0, %1" : "=s"(lo) : "i"((uint32_t)mask));
-    asm volatile("s_mov_b32 %0, %1" : "=s"(hi) : "i"((uint32_t)(mask >> 32)));
-    return __builtin_amdgcn_inverse_ballot_w64(((uint64_t)hi << 32) | lo);
-}
+static_assert(networks_sort<1>(64, 0) && networks_sort<1>(64, 5), "64-key network");
+static_assert(networks_sort<2>(128, 1) && networks_sort<4>(256, 3), "128- and 256-key networks");
+static_assert(networks_sort<1>(32, 0) && networks_sort<1>(32, 7), "two 32-key networks");
 
 // Ascending sort of 64*KPL keys held KPL per lane; element index r*64 + lane.
 template <int KPL>
 __device__ __forceinline__ void wave_sort(uint32_t (&v)[KPL]) {
     constexpr int N = kWave * KPL;
+    uint32_t lane = (uint32_t)lane_id();
+    asm volatile("" : "+v"(lane));   // the steps' lanes are not held across the caller's loops
 #pragma unroll
     for (int size = 2; size <= N; size <<= 1) {
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            if (size >= kWave && size < N && (r * kWave & size)) v[r] = ~v[r];
 #pragma unroll
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
             if (stride >= kWave) {
@@ -422,22 +426,24 @@ __device__ __forceinline__ void wave_sort(uint32_t (&v)[KPL]) {
                 for (int r = 0; r < KPL; ++r) {
                     const int p = r ^ rs;
                     if (p > r) {
-                        const bool asc = ((r * kWave) & size) == 0;
-                        uint32_t a = v[r], b = v[p];
-                        uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
-                        v[r] = asc ? lo : hi;
-                        v[p] = asc ? hi : lo;
+                        const uint32_t x = v[r], y = v[p];
+                        v[r] = min(x, y);
+                        v[p] = max(x, y);
                     }
                 }
             } else {
 #pragma unroll
                 for (int r = 0; r < KPL; ++r) {
-                    uint32_t o = xor_lanes_c(v[r], stride);
-                    uint32_t lo = v[r] < o ? v[r] : o, hi = v[r] < o ? o : v[r];
-                    v[r] = lanes_of(keep_low_lanes(size, stride, r)) ? lo : hi;
+                    const uint32_t o = stride == size >> 1 && size <= kWave
+                                           ? mirror_lanes(v[r], size)
+                                           : xor_lanes_c(v[r], stride);
+                    v[r] = keep_of(v[r], o, high_lanes(lane, stride));
                 }
             }
         }
+#pragma unroll
+        for (int r = 0; r < KPL; ++r)
+            if (size >= kWave && size < N && (r * kWave & size)) v[r] = ~v[r];
     }
 }
 
@@ -637,16 +643,16 @@ __device__ __forceinline__ uint32_t sketch_window_rare(const Word* W, uint32_t x
                                   (MC_LDS uint32_t*)scratch);
 }
 
-// Ascending bitonic sort of each 32-lane half of the wave (one key per lane).
+// Ascending sort of each 32-lane half of the wave (one key per lane).
 __device__ __forceinline__ void wave_sort_halves(uint32_t& v) {
+    uint32_t lane = (uint32_t)lane_id();
+    asm volatile("" : "+v"(lane));   // (as in wave_sort)
 #pragma unroll
     for (int size = 2; size <= 32; size <<= 1) {
+        v = keep_of(v, mirror_lanes(v, size), high_lanes(lane, size >> 1));
 #pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            uint32_t o = xor_lanes_c(v, stride);
-            uint32_t lo = v < o ? v : o, hi = v < o ? o : v;
-            v = lanes_of(keep_low_lanes(size, stride, 0, true)) ? lo : hi;
-        }
+        for (int stride = size >> 2; stride > 0; stride >>= 1)
+            v = keep_of(v, xor_lanes_c(v, stride), high_lanes(lane, stride));
     }
 }
 

@@ -1096,17 +1096,12 @@ __device__ __forceinline__ void large_lookup_cond(const QueryArgs& a, LargeLds& 
 // bitonic merge; element lane * K + r of the wave in v[r]. top <= 64 * K.
 template <int K>
 __device__ __forceinline__ void merge_steps(uint32_t (&v)[K], int top) {
-    const int lane = lane_id();
 #pragma unroll
     for (int stride = 32 * K; stride >= K; stride >>= 1) {
         if (stride >= top) continue;
-        const bool low = (lane & (stride / K)) == 0;
+        const uint32_t high = high_lanes((uint32_t)lane_id(), stride / K);
 #pragma unroll
-        for (int r = 0; r < K; ++r) {
-            const uint32_t o = xor_lanes_c(v[r], stride / K);
-            const uint32_t lo = v[r] < o ? v[r] : o, hi = v[r] < o ? o : v[r];
-            v[r] = low ? lo : hi;
-        }
+        for (int r = 0; r < K; ++r) v[r] = keep_of(v[r], xor_lanes_c(v[r], stride / K), high);
     }
 #pragma unroll
     for (int stride = K / 2; stride >= 1; stride >>= 1) {
