@@ -40,12 +40,14 @@ __device__ __forceinline__ uint32_t part_of(uint32_t f, uint64_t nb, uint32_t sh
 //                   partitions per scatter group (the group of a tile's pairs
 //                   is that of the level-1 scatter chunk holding the tile).
 //
-// Bound by vector and scalar issue (198 VALU and 179 SALU instructions a pair of
-// windows): the usual pair, two full windows whose candidates decide them, takes
-// a path of its own that stores its sketches from the registers that ranked
-// them. Against one path for every pair, booleans for its decisions and an
-// out-of-line redo of every window its first threshold did not decide: 280 and
-// 259 instructions, 9.8 -> 7.1 ms on a 4 Gbp build.
+// Bound by vector issue (171 VALU, eight of them quarter-rate multiplications of
+// the hash, and 154 SALU instructions a pair of windows; 6.3 ms on a 4 Gbp
+// build): the usual pair, two full windows whose candidates decide them, takes a
+// path of its own that stores its sketches from the registers that ranked them.
+// Against one path for every pair, booleans for its decisions and an out-of-line
+// redo of every window its first threshold did not decide: 280 and 259 -> 198 and
+// 179 instructions, 9.8 -> 7.1 ms; the rest is the sorting network and the
+// packing of the bases.
 //
 // Eight waves a SIMD: left unbounded, the kernel takes 106 scalar registers
 // and fewer waves fit; the scalar spills that the 8-wave budget costs are
@@ -101,7 +103,7 @@ void k_sketch(BuildArgs a) {
             const uint32_t nkB = !two ? 0u : j + 2u < td.nw ? a.S : nk_last;
             const uint32_t xA = xt + wv * a.S, xB = two ? xA + a.S : 0u;
             PairSketch p = sketch_pair<KPL>(L.words, xA, nkA, L.words, xB, nkB, a.k, a.s, th,
-                                            L.scratch[wave], dirty, dirty);
+                                            L.scratch[wave], dirty, dirty, (uint32_t)lane);
             if (kPairs) {
                 // both sketches full: every selected lane stores its pair
                 unsigned long long* const out = tile_out + wv * a.s;

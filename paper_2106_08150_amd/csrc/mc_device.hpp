@@ -187,12 +187,21 @@ __device__ __forceinline__ uint32_t rc_word(uint32_t code) {
     return ((r >> 1) & 0x55555555u) | ((r & 0x55555555u) << 1);
 }
 
-// Four 2-bit fields held in bits 8i..8i+1 (i = byte) packed into one byte,
-// byte 0's field in bits 7..6: reverse the bytes, then fold pairs twice.
-__device__ __forceinline__ uint32_t pack_fields(uint32_t v) {
-    const uint32_t r = __builtin_amdgcn_perm(0u, v, 0x00010203u);
-    const uint32_t t = r | (r >> 6);
-    return (t | (t >> 12)) & 0xFFu;
+// Four 2-bit fields held in bits 8i..8i+1 (i = byte) packed below acc's bits,
+// byte 0's field first (bits 7..6): a dot product with the fields' weights, one
+// instruction for four (with the candidate lanes of a pair of windows as a scalar
+// mask: 650 -> 635 vector instructions a 150-base read, 187 -> 171 a pair of
+// windows of the build).
+__device__ __forceinline__ uint32_t pack_fields(uint32_t v, uint32_t acc = 0u) {
+    return __builtin_amdgcn_udot4(v, 0x01041040u, acc, false);
+}
+// The same in the opposite order (byte 0's field in bits 1..0).
+__device__ __forceinline__ uint32_t pack_fields_back(uint32_t v) {
+    return __builtin_amdgcn_udot4(v, 0x40100401u, 0u, false);
+}
+// 0b11 for each byte of v that is 1, in the order of pack_fields.
+__device__ __forceinline__ uint32_t pack_flags(uint32_t v, uint32_t acc = 0u) {
+    return __builtin_amdgcn_udot4(v, 0x030C30C0u, acc, false);
 }
 
 // Codes of 4 ASCII bytes x (byte 0 = first base). Bits 1..2 of a letter give
@@ -217,12 +226,10 @@ __device__ __forceinline__ bool encode4(uint32_t x, uint32_t ok, uint32_t& c8, u
                                         uint32_t& r8) {
     uint32_t c;
     const uint32_t bad = codes4(x, c) & ok;                      // 0x80 per non-base inside
-    const uint32_t cc = c ^ 0x03030303u;
-    const uint32_t t2 = cc | (cc >> 6);
-    r8 = (t2 | (t2 >> 12)) & 0xFFu;
+    r8 = pack_fields_back(c ^ 0x03030303u);
     const uint32_t inv = bad | (~ok & 0x80808080u);               // 0x80 per invalid base
     c8 = pack_fields(c);
-    m8 = pack_fields((inv >> 6) | (inv >> 7));
+    m8 = pack_flags(inv >> 7);
     return bad != 0u;
 }
 
@@ -262,13 +269,14 @@ __device__ __forceinline__ Word load_word(uintptr_t a, uintptr_t vlo, uintptr_t 
         bad |= (inv[0] | inv[1] | inv[2] | inv[3]) != 0u;
     }
     Word w;
-    w.code = (pack_fields(c[0]) << 24) | (pack_fields(c[1]) << 16) | (pack_fields(c[2]) << 8) |
-             pack_fields(c[3]);
+    w.code = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w.code = pack_fields(c[i], w.code << 8);
     w.mask = 0u;
     if ((inv[0] | inv[1] | inv[2] | inv[3]) != 0u) {
         uint32_t m = 0u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) m = (m << 8) | pack_fields((inv[i] >> 6) | (inv[i] >> 7));
+        for (int i = 0; i < 4; ++i) m = pack_flags(inv[i] >> 7, m << 8);
         w.mask = m;
     }
     w.rc = rc_word(w.code);
@@ -351,6 +359,14 @@ __device__ __forceinline__ bool kmer_at(const Word* W, uint32_t x, uint32_t k, u
 // (692 -> 650 vector and 619 -> 526 scalar instructions a read), the sketches
 // of 4 Gbp 7.1 -> 6.4 ms.
 
+// The lane id as a value of this place: what is computed from it is not held
+// in registers across the enclosing loops.
+__device__ __forceinline__ uint32_t lane_here() {
+    uint32_t lane = (uint32_t)lane_id();
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 // All ones in the lanes with bit m (a power of two) of the lane id set.
 __device__ __forceinline__ uint32_t high_lanes(uint32_t lane, int m) {
     return 0u - (lane / (uint32_t)m & 1u);
@@ -411,8 +427,7 @@ static_assert(networks_sort<1>(32, 0) && networks_sort<1>(32, 7), "two 32-key ne
 template <int KPL>
 __device__ __forceinline__ void wave_sort(uint32_t (&v)[KPL]) {
     constexpr int N = kWave * KPL;
-    uint32_t lane = (uint32_t)lane_id();
-    asm volatile("" : "+v"(lane));   // the steps' lanes are not held across the caller's loops
+    const uint32_t lane = lane_here();
 #pragma unroll
     for (int size = 2; size <= N; size <<= 1) {
 #pragma unroll
@@ -644,9 +659,7 @@ __device__ __forceinline__ uint32_t sketch_window_rare(const Word* W, uint32_t x
 }
 
 // Ascending sort of each 32-lane half of the wave (one key per lane).
-__device__ __forceinline__ void wave_sort_halves(uint32_t& v) {
-    uint32_t lane = (uint32_t)lane_id();
-    asm volatile("" : "+v"(lane));   // (as in wave_sort)
+__device__ __forceinline__ void wave_sort_halves(uint32_t& v, uint32_t lane) {
 #pragma unroll
     for (int size = 2; size <= 32; size <<= 1) {
         v = keep_of(v, mirror_lanes(v, size), high_lanes(lane, size >> 1));
@@ -735,7 +748,8 @@ __device__ __forceinline__ uint32_t half_candidates(const Word* W, uint32_t x0, 
 // (A's below lane 32), each the rank-th of its window; dA and dB are the numbers
 // of distinct candidates. When full(s), these are the two sketches; else
 // sketch_rest completes them. scratch: 64 words of LDS owned by the wave. dirtyA
-// / dirtyB (wave-uniform): the window may hold an invalid base.
+// / dirtyB (wave-uniform): the window may hold an invalid base. sort_lane: the
+// lane id, from which the sort's lane constants are made.
 struct PairSketch {
     uint32_t v, rank;
     uint64_t sel;
@@ -749,7 +763,7 @@ __device__ __forceinline__ PairSketch sketch_pair(const Word* WA, uint32_t xA, u
                                                   const Word* WB, uint32_t xB, uint32_t nkB,
                                                   uint32_t k, uint32_t s, const Threshold& th,
                                                   uint32_t* scratch, uint32_t dirtyA,
-                                                  uint32_t dirtyB) {
+                                                  uint32_t dirtyB, uint32_t sort_lane) {
     const int lane = lane_id();
     PairSketch p;
     uint32_t most = 0;
@@ -759,11 +773,12 @@ __device__ __forceinline__ PairSketch sketch_pair(const Word* WA, uint32_t xA, u
     // leaves both windows undecided: no candidate stands for it
     if (__builtin_expect(ballot(most == 0xFFFFFFFFu) != 0ull, 0)) p.stateA = p.stateB = kUndecided;
     wave_lds_sync();
-    const uint32_t hl = (uint32_t)lane & 31u;
     const uint32_t word = scratch[lane];
-    uint32_t v = hl < ((lane < 32 ? p.stateA : p.stateB) & 63u) ? word : 0xFFFFFFFFu;
+    const uint32_t inA = (uint32_t)((1ull << (p.stateA & 63u)) - 1ull);   // at most 32 each
+    const uint32_t inB = (uint32_t)((1ull << (p.stateB & 63u)) - 1ull);
+    uint32_t v = lane_in((uint64_t)inB << 32 | inA) ? word : 0xFFFFFFFFu;
     wave_lds_sync();
-    wave_sort_halves(v);
+    wave_sort_halves(v, sort_lane);
     // previous lane's key (whole-wave shift right by one lane)
     const uint32_t prev = (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x138, 0xF, 0xF, false);
     // first of its value in its half: not the padding key, and lane 0 of the

@@ -701,7 +701,7 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
         wave_lds_sync();
         const Word *const WA = L.sk.stage, *const WB = L.sk.stage + kStageWords;
         PairSketch ps = sketch_pair<KPL>(WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s,
-                                         th, L.sk.scratch, dirtyA, dirtyB);
+                                         th, L.sk.scratch, dirtyA, dirtyB, lane_here());
         sketch_rest<KPL>(ps, WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s,
                          L.sk.feats + nf, L.sk.feats + nf + a.s, L.sk.scratch);
         const uint32_t nA = ps.nA, nB = ps.nB;
@@ -1302,7 +1302,7 @@ __device__ void classify_large_record(const QueryArgs& a, uint32_t rec, LargeLds
             wave_lds_sync();
             const Word *const WA = W.stage, *const WB = W.stage + kStageWords;
             PairSketch ps = sketch_pair<KPL>(WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k,
-                                             a.s, th, W.scratch, dirtyA, dirtyB);
+                                             a.s, th, W.scratch, dirtyA, dirtyB, lane);
             sketch_rest<KPL>(ps, WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s, W.sk,
                              W.sk + 64, W.scratch);
             const uint32_t nA = ps.nA, nB = ps.nB;
@@ -1463,7 +1463,7 @@ __device__ void classify_huge_record(const QueryArgs& a, uint32_t rec, const Hug
         wave_lds_sync();
         const Word *const WA = L.stage[wave], *const WB = L.stage[wave] + kStageWords;
         PairSketch ps = sketch_pair<KPL>(WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s,
-                                         th, L.scratch[wave], dirtyA, dirtyB);
+                                         th, L.scratch[wave], dirtyA, dirtyB, lane);
         sketch_rest<KPL>(ps, WA, wr[0].x0, wr[0].nk, WB, wr[1].x0, wr[1].nk, a.k, a.s, L.sk[wave],
                          L.sk[wave] + 64, L.scratch[wave]);
         const uint32_t nA = ps.nA, nB = ps.nB;
