@@ -156,8 +156,8 @@ __device__ __forceinline__ bool lookup_batch(const QueryArgs& a, const u64x2* sl
     // a batch; a wave's hit masks in scalar registers took 15 scalar
     // instructions a slot and step more. With the requeue once a batch and the
     // shorter record header, 10M reads of 150 bases on 4 Gbp: 757 -> 619
-    // scalar instructions a read, 14.84 -> 13.5 ms (385M random lines alone
-    // would take 10 ms).
+    // scalar instructions a read, 14.84 -> 13.5 ms (12.5 with the sorting
+    // networks of today; 385M random lines alone would take 10 ms).
     uint32_t nh = 0, fl = 0;
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
@@ -888,9 +888,9 @@ void k_classify(QueryArgs a, int cls) {
 // One wave a record with a bitonic sort in LDS and a scan over each range (the
 // form this replaces) left most of the chip idle and took O(range) steps per
 // location: 20,000 reads of 0.8 to 10 kbp on 1 Gbp (11,530 records of about
-// 1,450 locations) 296 -> 0.97 ms, 4,000 mixed records on 300 identical genomes
-// (3,792 records of about 5,800) 336 -> 0.75 ms. Of that, sketches and lookups
-// take 0.70 and 0.41 ms, sorting and ranking 0.27 and 0.34 ms.
+// 1,450 locations) 296 -> 0.85 ms, 4,000 mixed records on 300 identical genomes
+// (3,792 records of about 5,800) 336 -> 0.68 ms (0.97 and 0.75 before the sorting
+// networks without directions; sorting and ranking were 0.27 and 0.34 of that).
 constexpr int kLargeWaves = 8;
 constexpr int kLargeThreads = kLargeWaves * kWave;
 constexpr uint32_t kLargeFeats = 1024;   // sketch elements buffered before lookups
