@@ -75,9 +75,11 @@ struct Workspace {
     unsigned long long* qstats = nullptr;    // kQsWords
     unsigned char* huge = nullptr;           // kHugeBytes (HBM-list pass)
     uint32_t huge_groups = 0;                // regions in huge (0 = kHugeGroups)
+    bool ready = false;                      // allocated and cleared (init_workspace)
     bool recount = false;                    // the queue counts may not be zero (a launch failed)
+    bool own_counts = false;                 // the counts are zero at every start: one graph's
+                                             // replays only, or cleared just before
 };
-
 
 
 // Event pairs bracketing profiled launches.
@@ -760,24 +762,48 @@ int check_db(mc_db* db) {
     return MC_OK;
 }
 
+// Whether work queued on st is recorded instead of run (the default stream
+// cannot be captured).
+bool is_capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return st != nullptr && hipStreamIsCapturing(st, &s) == hipSuccess &&
+           s != hipStreamCaptureStatusNone;
+}
+
 // Device buffers of a workspace that do not depend on the batch size: the
 // counters and the HBM-list scratch, whose per-target bests start at zero
-// (the pass leaves them at zero).
+// (the pass leaves them at zero). After a failure the workspace is not ready
+// and the next call goes on from there. On a capturing stream the clearing
+// runs on a stream of its own: recorded, it would not have run yet for a plain
+// call before the first replay.
 int init_workspace(Workspace& w, hipStream_t st) {
-    if (int rc = dev_alloc(&w.counters, kNumQueryCounters)) return rc;
-    if (int rc = dev_alloc(&w.qstats, kQsWords)) return rc;
-    if (int rc = dev_alloc(&w.huge, kHugeBytes)) return rc;
-    if (int rc = dev_alloc(&w.route_meta, kRouteMetaWords)) return rc;
-    HIP_TRY(launch_clear_workspace(w.counters, w.huge, kHugeGroups, w.qstats, st));
+    if (w.ready) return MC_OK;
+    if (!w.counters)
+        if (int rc = dev_alloc(&w.counters, kNumQueryCounters)) return rc;
+    if (!w.qstats)
+        if (int rc = dev_alloc(&w.qstats, kQsWords)) return rc;
+    if (!w.huge)
+        if (int rc = dev_alloc(&w.huge, kHugeBytes)) return rc;
+    if (!w.route_meta)
+        if (int rc = dev_alloc(&w.route_meta, kRouteMetaWords)) return rc;
+    if (is_capturing(st)) {
+        hipStream_t cs = nullptr;
+        HIP_TRY(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+        hipError_t e = launch_clear_workspace(w.counters, w.huge, kHugeGroups, w.qstats, cs);
+        if (e == hipSuccess) e = hipStreamSynchronize(cs);
+        (void)hipStreamDestroy(cs);
+        HIP_TRY(e);
+    } else {
+        HIP_TRY(launch_clear_workspace(w.counters, w.huge, kHugeGroups, w.qstats, st));
+    }
+    w.ready = true;
     return MC_OK;
 }
 
 Workspace* workspace(mc_db* db, hipStream_t st, uint64_t n_records, int* rc) {
     Workspace& w = db->ws[st];
     *rc = MC_OK;
-    if (!w.huge) {
-        if ((*rc = init_workspace(w, st))) return nullptr;
-    }
+    if ((*rc = init_workspace(w, st))) return nullptr;
     if (n_records > w.queue_cap) {
         uint32_t* q = nullptr;
         const uint64_t c = std::max<uint64_t>(std::max<uint64_t>(n_records, 1024), 2 * w.queue_cap);
@@ -875,28 +901,26 @@ int launch_fast_phase(mc_db* db, const QueryArgs& a, Workspace& w, const LaunchP
 int classify_launch(mc_db* db, const char* reads, const uint64_t* offsets, uint32_t n_records,
                     const mc_query_opts& opts, uint32_t* out_labels, mc_tophit* out_top,
                     Workspace& w, const LaunchPlan& plan, hipStream_t st, bool profile) {
-    static_assert(kQOverflow == 0 && kQHuge == 1 && kQTooLong == 2 && kQDone == 3,
-                  "all counters but kQTooLong are a launch's own");
-    // the passes leave the queue counts at zero; cleared here only after a
-    // sequence of launches that did not reach the last pass
-    if (w.recount) {
-        HIP_TRY(launch_fill_u32(w.counters, 2, 0u, st));
-        HIP_TRY(launch_fill_u32(w.counters + kQDone, kNumQueryCounters - kQDone, 0u, st));
-    }
-    const bool was = w.recount;
-    w.recount = true;
+    static_assert(kQTooLong + 1 == kNumQueryCounters, "all the others are a launch's own");
+    // The passes leave the queue counts at zero, and what they read from counts
+    // that are not is past the batch. They are cleared here after a sequence of
+    // launches that did not reach the last pass, and in a sequence that is
+    // captured from a caller's stream (such a sequence may precede its replay).
+    const bool capturing = is_capturing(st);
+    if (capturing ? !w.own_counts : w.recount)
+        HIP_TRY(launch_fill_u32(w.counters, kQTooLong, 0u, st));
+    if (!capturing) w.recount = true;
     const QueryArgs a = query_args(db, reads, offsets, n_records, opts, out_labels, out_top, w);
     if (int rc = launch_fast_phase(db, a, w, plan, st, profile)) return rc;
     HIP_TRY(launch_classify_large(a, st, 0));
-    // a clearing that was only captured has not run yet
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    w.recount = was && (hipStreamIsCapturing(st, &cap) != hipSuccess ||
-                        cap != hipStreamCaptureStatusNone);
+    if (!capturing) w.recount = false;
     return MC_OK;
 }
 
+// The workspace of one graph.
 int alloc_workspace(Workspace& w, uint64_t n_records, hipStream_t st) {
     if (int rc = init_workspace(w, st)) return rc;
+    w.own_counts = true;
     w.queue_cap = std::max<uint64_t>(n_records, 1);
     return dev_alloc(&w.queue, 3 * w.queue_cap);
 }
@@ -1010,6 +1034,7 @@ int classify_into(struct ::mc_db* db, const char* reads, const uint64_t* offsets
     w.queue_cap = scratch.queue_cap;
     w.huge = scratch.huge;
     w.huge_groups = scratch.huge_groups;
+    w.own_counts = true;
     // what the passes expect at zero: the counters and the per-target bests
     HIP_TRY(launch_clear_workspace(w.counters, w.huge, scratch.huge_groups, nullptr, st));
     return classify_launch(db, reads, offsets, n_records, *opts, out_labels, out_top, w, db->plan,

@@ -108,12 +108,13 @@ inline uint32_t scatter_chunk_tiles(uint32_t s) {
 enum QueryCounter {
     kQOverflow = 0,      // records queued for the large-list pass
     kQHuge = 1,          // records queued for the HBM-list path (places taken in its queue)
-    kQTooLong = 2,       // records beyond every pass's capacity (left unclassified)
-    kQDone = 3,          // workgroups of the large-list pass that have finished
-    kQHugeReady = 4,     // records written to the HBM-list queue
-    kQHugeNext = 5,      // records taken from it
-    kQHugeBusy = 6,      // regions of the HBM-list scratch in use (bit mask)
-    kNumQueryCounters = 8
+    kQDone = 2,          // workgroups of the large-list pass that have finished
+    kQHugeReady = 3,     // records written to the HBM-list queue
+    kQHugeNext = 4,      // records taken from it
+    kQHugeBusy = 5,      // regions of the HBM-list scratch in use (bit mask)
+    kQTooLong = 6,       // records beyond every pass's capacity (left unclassified);
+                         // the others are back at zero after every classification
+    kNumQueryCounters = 7
 };
 
 // HBM-list path: one workgroup of the large-list pass a record, its lists in

@@ -1744,7 +1744,7 @@ void k_classify_large(QueryArgs a) {
         if (!uniform(s_job)) return;
         last = true;
     }
-    if (threadIdx.x < kNumQueryCounters && threadIdx.x != kQTooLong) a.counters[threadIdx.x] = 0u;
+    if (threadIdx.x < kQTooLong) a.counters[threadIdx.x] = 0u;
 }
 
 __global__ __launch_bounds__(256) void k_clear_workspace(uint32_t* counters, unsigned char* huge,
