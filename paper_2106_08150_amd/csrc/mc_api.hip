@@ -216,10 +216,20 @@ hipError_t release_idle(BlockCache& c, int device) {
     return err;
 }
 
+// hipMalloc whose failure is reported by its status alone. Left as the
+// runtime's last error, it would be taken for the failure of the next launch:
+// of this call where it goes on without the block (table growth without its
+// list), or of a later call of anyone's.
+hipError_t device_malloc(void** p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 int block_alloc(void** p, size_t bytes) {
     *p = nullptr;
     if (bytes < kCacheMinBytes) {
-        HIP_TRY(hipMalloc(p, bytes));
+        HIP_TRY(device_malloc(p, bytes));
         return MC_OK;
     }
     int dev = 0;
@@ -234,11 +244,9 @@ int block_alloc(void** p, size_t bytes) {
         c.idle.erase(it);
         return MC_OK;
     }
-    hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
+    if (device_malloc(p, bytes) != hipSuccess) {
         (void)release_idle(c, dev);
-        HIP_TRY(hipMalloc(p, bytes));
+        HIP_TRY(device_malloc(p, bytes));
     }
     c.live[*p] = {dev, bytes};
     return MC_OK;

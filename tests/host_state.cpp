@@ -301,6 +301,22 @@ void clearing_fails() {
     mc_db_destroy(db);
 }
 
+// Each allocation of a new workspace fails in turn.
+void allocation_fails() {
+    for (int k = 0; k < 5; ++k) {
+        mc_db* db = database();
+        int left = 2 * k;   // (a block that is kept for reuse is tried twice)
+        g_fail_alloc = [&](size_t) { return left-- <= 0; };
+        for (int tries = 0; tries < 12; ++tries) {
+            left = k;
+            if (classify(db) == MC_OK) break;
+        }
+        g_fail_alloc = [](size_t) { return false; };
+        expect(classify(db), MC_OK, "call after a failed allocation");
+        mc_db_destroy(db);
+    }
+}
+
 // A sequence that stops after its fast pass leaves counts behind: the next
 // call, a replay of an earlier capture and a new capture start at zero.
 void sequence_stops() {
@@ -344,14 +360,60 @@ void graph_calls() {
     mc_db_destroy(db);
 }
 
+// A table with entries whose growth needs a list of its own (the add's scratch
+// is smaller than the list).
+mc_db* filled(uint64_t* used) {
+    mc_db* db = database();
+    mc_insert_path path{};
+    path.chunk_slots = 4096;
+    mc_db_set_insert_path(db, &path);
+    const uint32_t n = 40, len = 1 << 18;
+    std::vector<char> text((size_t)n * len, 'A');
+    std::vector<uint64_t> lengths(n, len);
+    std::vector<uint32_t> taxa(n, 1);
+    expect(mc_db_add_targets(db, text.data(), lengths.data(), taxa.data(), n), MC_OK, "add");
+    *used = (uint64_t)n * ((len - 16 + 1 + 112) / 113) * 16;
+    return db;
+}
+
+// The list for a growth cannot be allocated: the entries are re-inserted, as
+// they are where no list is used.
+void growth_list_fails() {
+    uint64_t used = 0;
+    mc_db* db = filled(&used);
+    g_calls.clear();
+    const size_t list = (used / 16 + 4096) * 8;
+    int refused = 0;
+    g_fail_alloc = [&](size_t n) { return n == list && ++refused; };
+    expect(mc_db_reserve(db, 4 * used, 0.0), MC_OK, "growth without memory for its list");
+    g_fail_alloc = [](size_t) { return false; };
+    if (!refused) wrong("the growth asked for no list");
+    if (calls("grow_slices") || calls("rehash") != 1) wrong("growth: not by re-insertion");
+    mc_db_destroy(db);
+}
+
+// An allocation that failed is reported once: later calls do not see it.
+void refused_allocation_is_reported_once() {
+    mc_db* db = database();
+    g_fail_alloc = [](size_t n) { return n > (size_t(1) << 30); };
+    expect(mc_db_reserve(db, 1ull << 32, 0.0), MC_ERR_OOM, "table that does not fit");
+    g_fail_alloc = [](size_t) { return false; };
+    expect(classify(db), MC_OK, "classification after it");
+    if (hipGetLastError() != hipSuccess) wrong("the caller's next launch would report the allocation");
+    mc_db_destroy(db);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::map<std::string, void (*)()> all = {
         {"first_call_captured", first_call_captured},
         {"clearing_fails", clearing_fails},
+        {"allocation_fails", allocation_fails},
         {"sequence_stops", sequence_stops},
         {"graph_calls", graph_calls},
+        {"growth_list_fails", growth_list_fails},
+        {"refused_allocation_is_reported_once", refused_allocation_is_reported_once},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();
