@@ -430,7 +430,8 @@ __device__ __forceinline__ uint64_t div_by_S(const QueryArgs& a, uint64_t n) {
 }
 
 // Windows of a mate of len bases, and the windows of reference a fragment of
-// F bases can touch (sws).
+// F bases can touch (sws; at most those of the longest target, so that the end
+// of a range, its first window plus sws, does not wrap).
 __device__ __forceinline__ uint64_t mate_windows(const QueryArgs& a, uint64_t len) {
     return len < a.k ? 0 : div_by_S(a, len - a.k + a.S);
 }
@@ -442,7 +443,8 @@ __device__ __forceinline__ uint32_t mate_windows32(const QueryArgs& a, uint32_t 
     return (t + ((x - t) >> a.divS.sh1)) >> a.divS.sh2;
 }
 __device__ __forceinline__ uint32_t fragment_sws(const QueryArgs& a, uint64_t F) {
-    return F < a.k ? 1u : (uint32_t)(div_by_S(a, F - a.k + a.S - 1) + 1);
+    return F < a.k ? 1u
+                   : (uint32_t)min(div_by_S(a, F - a.k + a.S - 1) + 1, (uint64_t)1 << kWindowBits);
 }
 // The same for a fragment below 2^32 bases: F - k + S - 1 fits 32 bits unless
 // F lies within 512 of 2^32 (S is at most 256).
@@ -450,7 +452,7 @@ __device__ __forceinline__ uint32_t fragment_sws32(const QueryArgs& a, uint32_t 
     if (F < a.k) return 1u;
     if (F > 0xFFFFFE00u) return fragment_sws(a, F);
     const uint32_t x = F - a.k + a.S - 1u, t = __umulhi(a.divS.m, x);
-    return ((t + ((x - t) >> a.divS.sh1)) >> a.divS.sh2) + 1u;
+    return min(((t + ((x - t) >> a.divS.sh1)) >> a.divS.sh2) + 1u, 1u << kWindowBits);
 }
 
 // One window of a record: its bytes [lo, hi) inside the mate [vlo, vhi), as
