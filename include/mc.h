@@ -107,8 +107,9 @@ typedef struct mc_db_stats {
     uint64_t condensed_bytes;  /* device bytes of the condensed layout (0 if
                                   none, see mc_db_condense)                 */
     uint64_t q_large_records;  /* records classify handed to its large-list
-                                  pass (list, or number of sketch elements,
-                                  over the launch's capacity)               */
+                                  pass (list over the launch's capacity, or on
+                                  its way there, or a long record with more
+                                  sketch elements than that)                */
     uint64_t q_hbm_records;    /* records handed on to the HBM-list pass
                                   (list over 16384 locations)               */
 } mc_db_stats;

@@ -641,6 +641,22 @@ __device__ __forceinline__ void label_short_list(const QueryArgs& a, uint32_t re
     write_result(a, rec, label_of(a, L, nsel), L, nsel);
 }
 
+// A record with more sketch elements than the fast pass's list holds may
+// outgrow it. From 2^kLongBits bases on it goes to the large-list pass at once,
+// whose eight waves share its windows (a wave takes about 2 us a window, and the
+// last records of a launch hold it up). A shorter one stays: each time its
+// buffered features have been looked up, the locations it would have in all at
+// the rate so far are compared with the list, and it goes on only when they
+// exceed it by a sixteenth. What a record holds decides, not its length alone:
+// a read of a stored genome has a location or more an element, one of an
+// organism that the database does not hold has few. 60 MB of reads on 100 Mbp,
+// list of 256 / 512, against handing on every record past the list's capacity:
+// foreign reads of 2,200 bases 1.01 / .22 -> .21 / .21 ms, of 5,000 .60 / .60 ->
+// .23 / .23, of 10,000 .49 either way (72 windows and more: eight waves each);
+// stored reads of 5,000 .66 -> .67 / .69; 20,000 reads of 0.8 to 10 kbp, 5%
+// foreign, on 1 Gbp 1.06 -> 1.09.
+constexpr uint32_t kLongBits = 13;
+
 template <uint32_t LCAP, int KPL, bool C>
 __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>& L,
                                 const Threshold& th, WaveStats& ws) {
@@ -652,21 +668,28 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
     const uint32_t at0 = a.paired;
     const uint64_t o0 = off[(uint64_t)rec << at0], o1 = off[((uint64_t)rec << at0) + 1];
     const uint64_t o2 = at0 ? off[((uint64_t)rec << at0) + 2] : o1;
-    // one test for every record that is not to be classified: with both
-    // lengths and their sum below 2^31 and no wrap past 2^64 the offsets
-    // ascend and the record is shorter than 2^31 bytes
+    // one test for every record that is not to be classified here: with both
+    // lengths and their sum below 2^kLongBits and no wrap past 2^64 the offsets
+    // ascend and the record is short
     const uint64_t d0 = o1 - o0, d1 = o2 - o1;
     RecordSpan rs;
     rs.len[0] = (uint32_t)d0;
     rs.len[1] = (uint32_t)d1;
     const uint32_t len = rs.len[0] + rs.len[1];
     if (__builtin_expect(((uint32_t)(d0 >> 32) | (uint32_t)(d1 >> 32) |
-                          ((rs.len[0] | rs.len[1] | len) >> 31)) != 0u ||
+                          ((rs.len[0] | rs.len[1] | len) >> kLongBits)) != 0u ||
                           (uint32_t)(o2 >> 32) < (uint32_t)(o0 >> 32), 0)) {
-        // malformed (nothing to classify), or too long for every pass
-        if (!(o1 < o0 || o2 < o1) && lane == 0) atomicAdd(&MC_COLD(counters)[kQTooLong], 1u);
-        write_result(a, rec, kNone, L, 0);
-        return;
+        const bool malformed = o1 < o0 || o2 < o1;   // nothing to classify
+        if (malformed || o2 - o0 >= (1ull << 31)) {  // or too long for every pass
+            if (!malformed && lane == 0) atomicAdd(&MC_COLD(counters)[kQTooLong], 1u);
+            write_result(a, rec, kNone, L, 0);
+            return;
+        }
+        if ((mate_windows32(a, rs.len[0]) + mate_windows32(a, rs.len[1])) * a.s > LCAP) {
+            if (lane == 0) MC_COLD(queue)[atomicAdd(&MC_COLD(counters)[kQOverflow], 1u)] = rec;
+            ws.passed_on += 1;
+            return;
+        }
     }
     const uintptr_t first = (uintptr_t)(a.reads + o0);
     rs.base = first & ~(uintptr_t)15;
@@ -689,11 +712,7 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
     }
     const uint32_t nwt = nws[0] + nws[1];
     uint32_t nlist = 0, nf = 0;
-    // a record with more sketch elements than the list holds most likely
-    // outgrows it (an element of a read from a stored genome has a location
-    // or more): it goes straight to the large-list pass, whose eight waves
-    // share its windows
-    bool fits = nwt * a.s <= LCAP;
+    bool fits = true;
     for (uint32_t p = 0; p < nwt && fits; p += 2) {
         WinRef wr[2];
         for (int h = 0; h < 2; ++h) wr[h] = window_ref(a, p + h, nwt, nws[0], rs.r0, rs.len);
@@ -726,6 +745,8 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
             else
                 fits = lookup<LCAP>(a, L.sk.feats, nf, L.ring, L.list, nlist, ws.probes);
             nf = 0;
+            // (after the last lookup the list holds all of its locations)
+            if (nlist * nwt > (LCAP + LCAP / 16) * (p + 2)) fits = false;
         }
     }
     if (!fits) {
