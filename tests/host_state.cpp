@@ -403,6 +403,36 @@ void refused_allocation_is_reported_once() {
     mc_db_destroy(db);
 }
 
+// More entries leave their slice than a growth's list holds: the growth starts
+// over. A conversion's list is made anew at the size it needs.
+void lists_too_short() {
+    uint64_t used = 0;
+    mc_db* db = filled(&used);
+    g_calls.clear();
+    expect(mc_db_reserve(db, 4 * used, 0.0), MC_OK, "growth");
+    if (calls("grow_slices") != 1 || calls("rehash")) wrong("growth: not by slices alone");
+    mc_insert_path path{};
+    path.defer_entries = 5;
+    mc_db_set_insert_path(db, &path);
+    g_calls.clear();
+    g_grow_deferred = 5;
+    expect(mc_db_reserve(db, 16 * used, 0.0), MC_OK, "growth with a list that just holds");
+    if (calls("grow_slices") != 1 || calls("rehash")) wrong("growth: started over without a reason");
+    g_calls.clear();
+    g_grow_deferred = 6;
+    expect(mc_db_reserve(db, 64 * used, 0.0), MC_OK, "growth with a list that is too short");
+    if (calls("grow_slices") != 1 || calls("rehash") != 1) wrong("growth: not started over");
+    g_calls.clear();
+    g_cond_deferred = 9;
+    expect(mc_db_condense(db, 0), MC_OK, "conversion with a list that is too short");
+    if (calls("condense_write") != 2 || g_cond_cap != 9) wrong("conversion: not repeated with a longer list");
+    g_calls.clear();
+    g_cond_deferred = 5;
+    expect(mc_db_condense(db, 0), MC_OK, "conversion with a list that just holds");
+    if (calls("condense_write") != 1) wrong("conversion: repeated without a reason");
+    mc_db_destroy(db);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -414,6 +444,7 @@ int main(int argc, char** argv) {
         {"graph_calls", graph_calls},
         {"growth_list_fails", growth_list_fails},
         {"refused_allocation_is_reported_once", refused_allocation_is_reported_once},
+        {"lists_too_short", lists_too_short},
     };
     if (argc != 2 || !all.count(argv[1])) return 2;
     all.at(argv[1])();

@@ -1,6 +1,7 @@
 """State that the host side keeps between calls, on a stand-in device (see
 host_state.cpp): a workspace whose first clearing failed or was captured, a
-sequence of launches that stops half way, allocations that fail.
+sequence of launches that stops half way, allocations that fail,
+growths and conversions whose lists prove too short.
 
 Needs a host compiler and the HIP headers, no GPU.
 """
@@ -14,7 +15,8 @@ from conftest import ROOT
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 SCENARIOS = ["first_call_captured", "clearing_fails", "sequence_stops", "graph_calls",
-             "allocation_fails", "growth_list_fails", "refused_allocation_is_reported_once"]
+             "allocation_fails", "growth_list_fails", "refused_allocation_is_reported_once",
+             "lists_too_short"]
 
 
 @pytest.fixture(scope="module")
