@@ -906,10 +906,11 @@ __global__ __launch_bounds__(256) void k_cap_scan(unsigned long long* table, uin
 // in it) go to `defer` (counters[kCntDefer] of them; those past defer_cap are
 // dropped, the caller then starts over with k_rehash).
 //
-// Bound by HBM bytes: the old table read once, the new one written once. One
-// global atomic per entry on its bucket's counter (k_rehash) left neighbouring
-// entries waiting on the same counters: 1.4M entries from 23 to 45 MB took
-// 541 us, now 28 (2.4 TB/s).
+// The old table is read once, the new one written once: 1.4M entries from 24 to
+// 47 MB take 28 us (2.5 TB/s, half of what a large copy reaches), bound by the
+// latency of a slice's phases (vector issue at 29% of its peak). One global
+// atomic per entry on its bucket's counter (k_rehash) left neighbouring entries
+// waiting on the same counters: 541 us.
 constexpr uint32_t kGrowCap = 3072;
 
 __global__ __launch_bounds__(kSliceThreads)

@@ -18,12 +18,13 @@
 // places the slice's features by a max-plus scan over its index buckets (as the
 // slice insert of the build does) and writes every index line once.
 //
-// Bound by vector issue (about 75% of its peak) and the bytes: two passes over
-// the table, the index written once. The form this replaces sorted each slice's
+// The write pass is bound by vector issue (72% of its peak) and the barriers
+// between its phases; it moves 5.7 GB at 3.1 TB/s, two thirds of what a large
+// copy reaches. The form this replaces sorted each slice's
 // 64-bit entries in LDS twice, claimed every index entry with a global atomic
 // and cleared the index first: a 1 Gbp table (2.3 GB, 141.6M pairs) took 9.8 ms
 // to count, 11.3 to write and 1.7 for the clearing, the scan and the pair count;
-// now 0.68 + 1.79 + 0.09 ms (5.9 GB moved by the write pass, 3.3 TB/s).
+// now 0.71 + 1.82 + 0.09 ms.
 #include "mc_device.hpp"
 #include "mc_internal.hpp"
 #include "mc_slices.hpp"
@@ -45,7 +46,8 @@ constexpr uint32_t kCondCountBins = kCondBuckets << kCondBinSplit;
 constexpr uint32_t kCondWriteBins = 2048;
 // Entries of one slice in the write pass's usual form: a table at the default
 // load holds about 2,048 (at most 4,096 slots); slices beyond it take the
-// kCondCap form. 52 KB of LDS against 120 KB: three workgroups a CU, not one.
+// kCondCap form. 52,088 bytes of LDS against 115,064: three workgroups a CU, not
+// one.
 constexpr uint32_t kCondMid = 2944;
 // A bin with more entries is sorted by the workgroup: the comparisons of every
 // entry with all others of its bin grow with the square.

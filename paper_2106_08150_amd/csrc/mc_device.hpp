@@ -390,9 +390,10 @@ __device__ __forceinline__ uint32_t mirror_lanes(uint32_t v, int size) {
     }
 }
 
-// Compile-time check: the networks of wave_sort (KPL keys a lane) and
-// wave_sort_halves, run on the host over a few key patterns, leave every
-// sequence ascending.
+// Compile-time check of the scheme described above (mirror first steps,
+// complemented odd blocks) on a model of its own over a few key patterns: every
+// sequence ends ascending. The model shares no code with the device networks;
+// those are tested on the device, for every number of keys a lane.
 template <int KPL>
 constexpr bool networks_sort(int top, uint32_t seed) {
     constexpr int N = 64 * KPL;

@@ -59,7 +59,7 @@ constexpr uint32_t kRingMirror = 32;
 template <uint32_t LCAP>
 struct QueryLds {
     uint2 ring[kRing + kRingMirror];  // (feature, bucket) lookup work items
-    uint32_t list[LCAP + kWave];      // one item batch may overshoot LCAP by < 64
+    uint32_t list[LCAP + kWave];      // waves read up to 63 entries past its end
     union {
         struct {
             Word stage[2 * kStageWords];
@@ -855,22 +855,26 @@ __device__ void classify_record(const QueryArgs& a, uint32_t rec, QueryLds<LCAP>
 
 // Occupancy: the lookups' memory latency is hidden by other waves' work, so
 // occupancy pays for a few spilled scalar registers. A 512-entry list takes
-// about 5.7 KB of LDS a wave, which holds a CU to 28 waves: seven a SIMD (at
-// most 72 VGPRs). A 256-entry list takes about 3.7 KB, so eight waves a SIMD
-// fit (64 VGPRs). A 1,024-entry list (9.7 KB) allows four waves a SIMD: its
-// register budget follows, so that no variant spills vector registers to
-// scratch memory (a kernel with scratch makes the runtime set up scratch for
-// the hardware queue it runs on, milliseconds on a queue's first such launch).
-// The condensed layout's lookups also fit eight waves at a 256-entry list
-// (63 VGPRs, more scalar spills than at seven, and 4% faster).
-template <uint32_t LCAP, bool C>
+// 5,736 bytes of LDS a wave, which holds a CU to 28 waves: seven a SIMD (at
+// most 72 VGPRs). A 256-entry list takes 4,064, so eight waves a SIMD fit (64
+// VGPRs), also with the condensed layout's lookups (63, more scalar spills than
+// at seven, and 4% faster). A 1,024-entry list (9,832) allows four.
+//
+// The 256- and 512-entry variants take no scratch memory; the 1,024-entry ones
+// take 40 bytes a lane (88 with the condensed layout), in which the out-of-line
+// sort of 1,024 entries saves registers. A kernel with scratch makes the runtime
+// set it up for the hardware queue it runs on: milliseconds on a queue's first
+// such launch, so the first classification with that list is slower than the rest.
+static_assert(sizeof(QueryLds<256>) == 4064 && sizeof(QueryLds<512>) == 5736 &&
+              sizeof(QueryLds<1024>) == 9832, "LDS a wave");
+template <uint32_t LCAP>
 constexpr int classify_waves_per_simd() {
     return LCAP <= 256 ? 8 : LCAP <= 512 ? 7 : 4;
 }
 
 template <uint32_t LCAP, int WPB, int KPL, bool C>
 __global__ __launch_bounds__(WPB * 64)
-__attribute__((amdgpu_waves_per_eu(classify_waves_per_simd<LCAP, C>())))
+__attribute__((amdgpu_waves_per_eu(classify_waves_per_simd<LCAP>())))
 void k_classify(QueryArgs a, int cls) {
     __shared__ QueryLds<LCAP> L[WPB];
     const int wave = (int)uniform(threadIdx.x >> 6);
@@ -912,8 +916,9 @@ void k_classify(QueryArgs a, int cls) {
 // form this replaces) left most of the chip idle and took O(range) steps per
 // location: 20,000 reads of 0.8 to 10 kbp on 1 Gbp (11,530 records of about
 // 1,450 locations) 296 -> 0.85 ms, 4,000 mixed records on 300 identical genomes
-// (3,792 records of about 5,800) 336 -> 0.68 ms (0.97 and 0.75 before the sorting
+// (3,792 records of about 5,800) 336 -> 0.70 ms (0.97 and 0.75 before the sorting
 // networks without directions; sorting and ranking were 0.27 and 0.34 of that).
+// Vector issue is at 46% and 43% of its peak there.
 constexpr int kLargeWaves = 8;
 constexpr int kLargeThreads = kLargeWaves * kWave;
 constexpr uint32_t kLargeFeats = 1024;   // sketch elements buffered before lookups
@@ -1892,8 +1897,13 @@ __global__ __launch_bounds__(256) void k_route_scatter(QueryArgs a, RouteConfig 
 
 // Workgroups of the large-list pass when the number of queued records is not
 // known on the host: as many as fit the chip at once (two a CU), at most one a
-// record. Without queued records they end at once: 512 of them cost no more
-// than 8 did (10,000 short reads: 25.6 us a call with either).
+// record. Without queued records they end at once, alone (10,000 short reads:
+// 25.6 us a call with 512 as with 8) and beside other streams, although each
+// needs half a CU's LDS for its moment: against 8 workgroups that take a whole
+// CU's (and launches of their own for the HBM-list records and the clearing of
+// the counts), calls of 200 reads on four streams in turn 12.4 -> 7.0 us a call,
+// of 20,000 reads 33 -> 27, of 200 reads beside a stream of 2M-read
+// classifications 7.4 -> 5.8 ms at the median (their time there 2.44 -> 1.91 ms).
 inline unsigned large_pass_groups(uint32_t n_records) {
     return (unsigned)std::min<uint32_t>(512u, n_records);
 }

@@ -241,9 +241,8 @@ struct mc_server {
     // its own; they come back with the results, and only chunks that passed
     // records on get the large-list pass. A large-list workgroup takes half of
     // a CU's LDS and starts only on a CU that other kernels have left so far:
-    // queued unconditionally next
-    // to other batches' kernels, it would hold up every batch until the
-    // device drains.
+    // queued unconditionally next to other batches' kernels, it would hold up
+    // its batch until they leave one.
     int process(Slot& s, Job& j) {
         Turn turn{copy_mu, copy_cv, copy_turn, j.order};
         Turn launch{launch_turn_mu, launch_cv, launch_turn, j.order};
